@@ -14,7 +14,7 @@ struct GemmLaunch {
   int K, N;       // N = output columns
   const uint16_t* aprep;  // activations in the prepared layout
   int M;
-  // non-null (plans with norm_in_kslice only): the input is RMSNorm(xnorm)
+  // non-null (plans that norm_in_ksplit accepts only): the input is RMSNorm(xnorm)
   // with weight gamma [K], computed in the GEMM; aprep is not read
   const uint16_t* xnorm = nullptr;
   int ldx = 0;
@@ -28,22 +28,25 @@ struct GemmLaunch {
   int nw;       // N-tiles (16 columns) per block, counting gate and up tiles for SwiGLU
   int nblocks;  // column blocks
   int nwg;      // workgroups launched
-  int ksw;      // > 0: one workgroup per column tile with ksw waves splitting K (no partials)
+  int ksw;      // > 0: K-split workgroups of ksw waves (no partials), knt weight tiles each
+  int knt;      // (counting gate and up tiles for SwiGLU)
   bool swiglu;
   float* part;  // split-K partial slots (2 per workgroup)
 };
 
 // A K-split GEMM applies the RMSNorm of its input itself where no wave
 // holds more than this many 128-wide groups (all its loads in registers).
-constexpr int kNormMaxGroupsPerWave = 4;
+constexpr int kNormGroupsPerWave = 2;
 
 struct GemmPlan {
-  int nw, nblocks, nwg, ksw = 0;
+  int nw, nblocks, nwg, ksw = 0, knt = 0;
   size_t part_bytes;  // split partials
   size_t prep_bytes;  // prepared activations of the input
 };
 GemmPlan plan_w4a16_gemm(int M, int K, int N, bool swiglu);
-bool norm_in_kslice(const GemmPlan& p, int K);
+// whether the GEMM of plan p applies the RMSNorm of its input itself; if so,
+// p becomes the plan of that form
+bool norm_in_ksplit(GemmPlan& p, int M, int K, int N, bool swiglu);
 void launch_w4a16_gemm(const GemmLaunch& L, hipStream_t st);
 void launch_prepare_activations(const uint16_t* x, int M, int ldx, int K, uint16_t* out, hipStream_t st);
 void launch_prepack_w4(const uint8_t* q, const uint16_t* s, const uint8_t* z, int K, int N, void* packed,

@@ -80,7 +80,8 @@ struct NormIn {
 };
 
 bool norm_in_gemm(int M, const swiftspec_w4* W0, bool swiglu) {
-  return ss::norm_in_kslice(ss::plan_w4a16_gemm(M, W0->K, W0->N, swiglu), W0->K);
+  ss::GemmPlan p = ss::plan_w4a16_gemm(M, W0->K, W0->N, swiglu);
+  return ss::norm_in_ksplit(p, M, W0->K, W0->N, swiglu);
 }
 
 void run_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16_t* aprep, int M,
@@ -90,6 +91,7 @@ void run_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16_t* ap
   ss::GemmPlan p = ss::plan_w4a16_gemm(M, W0->K, W0->N, swiglu);
   ss::GemmLaunch L;
   if (norm) {
+    ss::norm_in_ksplit(p, M, W0->K, W0->N, swiglu);
     L.xnorm = norm->x;
     L.ldx = norm->ldx;
     L.gamma = norm->gamma;
@@ -110,6 +112,7 @@ void run_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16_t* ap
   L.nblocks = p.nblocks;
   L.nwg = p.nwg;
   L.ksw = p.ksw;
+  L.knt = p.knt;
   L.swiglu = swiglu;
   L.part = part;
   ss::launch_w4a16_gemm(L, st);

@@ -38,12 +38,7 @@
 
 namespace ss {
 
-// EPI_SWIGLU_SPLIT: the fused SwiGLU with the gate and the up tile of an
-// output column in two different waves (waves 0, 1: gate tiles of the
-// block's two columns; waves 2, 3: their up tiles), combined through LDS at
-// the end: twice the waves of EPI_SWIGLU for the same columns, half the
-// dequantisation and MFMA work per wave and step.
-enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_SPLIT = 2 };
+enum { EPI_PLAIN = 0, EPI_SWIGLU = 1 };
 
 // Kernel-native copy of an int4 matrix (written by prepack_w4_kernel):
 //   q : [N/16 tiles][G groups][64 lanes] x 16 bytes -- lane kq*16 + c holds
@@ -99,9 +94,6 @@ struct GemmShape {
 };
 constexpr GemmShape gemm_shape(int MT, bool swiglu) {
   return MT > 2 ? GemmShape{3, 2, 512} : swiglu ? GemmShape{3, 2, 768} : GemmShape{3, 2, 512};
-}
-constexpr GemmShape gemm_shape_epi(int MT, int EPI) {
-  return EPI == EPI_SWIGLU_SPLIT ? GemmShape{MT == 1 ? 4 : 3, 4, 1 << 30} : gemm_shape(MT, EPI == EPI_SWIGLU);
 }
 constexpr int kRingL = 3;  // LDS ring of activation fragments
 
@@ -211,16 +203,13 @@ __device__ __forceinline__ float* part_slot(const GemmArgs& a, int v, int slot, 
 }
 
 template <int MT, int NWV, int EPI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(gemm_shape_epi(MT, EPI).occ)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(gemm_shape(MT, EPI == EPI_SWIGLU).occ)))
 void w4a16_gemm_kernel(GemmArgs a) {
-  constexpr bool kSplit = EPI == EPI_SWIGLU_SPLIT;
   constexpr int kColW = (EPI == EPI_SWIGLU) ? NWV / 2 : NWV;  // output column tiles per wave
-  constexpr int kColB = kSplit ? 2 : 4 * kColW;                // output column tiles per block
+  constexpr int kColB = 4 * kColW;                            // output column tiles per block
   constexpr int kSrc = (EPI == EPI_SWIGLU) ? 2 : 1;
-  constexpr int kRing = gemm_shape_epi(MT, EPI).ring;
-  static_assert(!kSplit || NWV == 1, "split SwiGLU: one tile per wave");
+  constexpr int kRing = gemm_shape(MT, EPI == EPI_SWIGLU).ring;
   __shared__ u32x4 abuf[kRingL][MT][4][kWave];  // activation fragments of 3 groups
-  __shared__ f32x4 xch[kSplit ? 2 : 1][MT][kWave];  // split SwiGLU: the up sums for the gate waves
 
   const int tid = threadIdx.x;
   const int lane = lane_id();
@@ -252,15 +241,15 @@ void w4a16_gemm_kernel(GemmArgs a) {
   // so a load costs no vector ALU work.
   const uint32_t q_bytes = (uint32_t)((size_t)a.K * a.N / 2), sz_bytes = (uint32_t)((size_t)a.N * G * 4);
   const auto rq0 = buffer_rsrc(a.w0.q, q_bytes), rs0 = buffer_rsrc(a.w0.sz, sz_bytes);
-  const auto rq1 = buffer_rsrc(EPI != EPI_PLAIN ? a.w1.q : a.w0.q, q_bytes);
-  const auto rs1 = buffer_rsrc(EPI != EPI_PLAIN ? a.w1.sz : a.w0.sz, sz_bytes);
+  const auto rq1 = buffer_rsrc(EPI == EPI_SWIGLU ? a.w1.q : a.w0.q, q_bytes);
+  const auto rs1 = buffer_rsrc(EPI == EPI_SWIGLU ? a.w1.sz : a.w0.sz, sz_bytes);
   const auto ra = buffer_rsrc(a.a, (uint32_t)(MT * G * 4 * kWave * 16));
   const uint32_t lane16 = (uint32_t)lane * 16u, col4 = (uint32_t)ncol * 4u;
   auto load_b = [&](BStage<MT, NWV>& st) {
-    const int tw = ld_nb * kColB + (kSplit ? (wave & 1) : wave * kColW);  // first column tile of this wave
+    const int tw = ld_nb * kColB + wave * kColW;  // first column tile of this wave
 #pragma unroll
     for (int nt = 0; nt < NWV; ++nt) {
-      const bool up = (EPI == EPI_SWIGLU && nt >= kColW) || (kSplit && wave >= 2);
+      const bool up = EPI == EPI_SWIGLU && nt >= kColW;
       const uint32_t tg = (uint32_t)((tw + nt % kColW) * G + ld_g);
       st.b[nt] = buffer_load_x4(up ? rq1 : rq0, lane16, tg * 1024u);
       st.sz[nt] = buffer_load_x1(up ? rs1 : rs0, col4, tg * 64u);
@@ -348,35 +337,7 @@ void w4a16_gemm_kernel(GemmArgs a) {
   // range's first N-block, slot 1: its last) for the fix-up kernel.
   auto flush = [&](int nb) {
     const bool full = (long)nb * G >= u_lo && (long)(nb + 1) * G <= u_hi;
-    if constexpr (kSplit) {
-      // every range holds whole blocks: the up waves hand their sums to the
-      // gate waves of the same columns, which write silu(gate) * up
-      if (wave >= 2) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) xch[wave - 2][mt][lane] = acc[mt][0];
-      }
-      __syncthreads();
-      if (wave < 2) {
-        const int col = (nb * kColB + wave) * 16 + ncol;
-        const int G2 = a.N >> 7;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const f32x4 u = xch[wave][mt][lane];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int m = mt * 16 + kq * 4 + r;
-            if (m < a.M) {
-              const float gte = acc[mt][0][r];
-              const uint16_t h = f2h(gte / (1.0f + __expf(-gte)) * u[r]);
-              if (a.y) a.y[(size_t)m * a.ldy + col] = h;
-              if (a.yp) store_prepared(a.yp, m, col, G2, h);
-            }
-          }
-        }
-      }
-      __syncthreads();  // the exchange buffer is free for the range's next block
-      (void)full;
-    } else if (full) {
+    if (full) {
       emit(nb);
     } else {
       float* mine = part_slot<MT, NWV, EPI>(a, v, nb == u_lo / G ? 0 : 1, wave);
@@ -427,7 +388,7 @@ void w4a16_gemm_kernel(GemmArgs a) {
   // barrier of step i has passed) and applies unit i - 1's sums.  Above 32
   // rows the second buffers would cost the second wave per SIMD, so step i
   // reads, multiplies and applies its own unit.
-  constexpr bool kPipe = MT <= 2 && !kSplit;
+  constexpr bool kPipe = MT <= 2;
   constexpr int kBuf = kPipe ? 2 : 1;
   half8 af[kBuf][MT][4];
   f32x4 cs[kBuf][MT][NWV];
@@ -551,133 +512,155 @@ __global__ __launch_bounds__(256) void w4a16_fixup_kernel(GemmArgs a) {
   ep.write(a, nb, wave, lane, acc, mt0 * 16);
 }
 
-// ------------------------------------------------- small M, small weights
-// Up to 16 rows and a few megabytes of weights (the 1B-shaped layer's and
-// the 8B-shaped layer's QKV and O projections, tensor-parallel shards) the
-// stream-K kernel's time is its fixed costs: first loads, the split
-// partials and the fix-up kernel.  Here one workgroup owns one 16-column
-// output tile over the whole K range: its W waves take contiguous group
-// ranges, each streaming its own weight blocks and activation fragments
-// (the prepared layout's four fragments of the group, straight into the
-// MFMA A operand) through a 3-deep register ring, and the W partial sums
-// are added in wave order through LDS (results deterministic), then wave 0
-// adds the residual and writes the tile.  No partials leave the workgroup
-// and no second kernel runs.  Every workgroup reads the whole activation
-// matrix (from L2): four times the weight bytes, which is why the plan
-// keeps it to small weights.
+// ------------------------------------------------------- K-split workgroups
+// One workgroup owns kC 16-column output tiles (a fused SwiGLU: their gate
+// and up tiles) over the whole K range; its W waves take contiguous group
+// ranges.  A wave streams its weight blocks (one group ahead) and its
+// activation fragments (the prepared layout's, straight into the MFMA A
+// operand, each M-tile's registers reloaded for the next group as soon as
+// its last product has read them) and nothing is shared until the W partial
+// sums are added in wave order through LDS: no barrier in the loop, no
+// partials in memory, no second kernel, results deterministic.
+//
+// What bounds it: every workgroup reads the whole activation matrix from L2
+// (about 11 TB/s over the chip), i.e. 4 MT / NT times its weight bytes, so
+// NT (weight tiles per workgroup) is the smallest that leaves about one
+// workgroup per compute unit, and shapes with both many rows and a long K
+// stay on the stream-K kernel, which shares the activations through LDS.
+// Up to 16 rows the rest is fixed cost (launch, first loads, the sum).
+// Measured against the kernels used before (us, weights rotated through
+// HBM; 8 / 32 / 64 rows): K 4096, N 4096 5.6 -> 4.9, 10.0 -> 5.8, 11.8 ->
+// 8.6; K 8192, N 8192 14.3 -> 12.2, 20.8 -> 15.1, 23.9 -> 21.0; K 8192, N
+// 10240 17.7 -> 14.6, 23.3 -> 19.5, 27.8 -> 26.6; K 2048, N 8192 6.0 ->
+// 4.5, 9.4 -> 5.3, 11.8 -> 6.7; SwiGLU K 8192, N 7168 16.5 -> 15.1, 28.3
+// -> 19.3, 32.9 -> 26.0; SwiGLU K 4096, N 14336 17.9 -> 15.9, 23.3 -> 19.2,
+// 32.5 -> 29.5.
 
-template <int W, int NT>
-__global__ __launch_bounds__(64 * W) void w4a16_kslice_kernel(GemmArgs a) {
-  constexpr int kR = 3;
-  static_assert(NT == 1 || NT == 2, "plain, or fused SwiGLU (gate and up tile of one column tile)");
-  __shared__ f32x4 red[W][NT][kWave];
+// The W waves' partial sums of a K-split workgroup (red, after the barrier)
+// added in wave order, and the workgroup's MT x kC output tiles written,
+// dealt to the waves.
+template <int W, int MT, int NT, bool SW>
+__device__ __forceinline__ void ksplit_write(const GemmArgs& a, const f32x4 (&red)[W][MT * NT][kWave], int t0, int wave,
+                                             int lane) {
+  constexpr int kC = SW ? NT / 2 : NT;
+  constexpr int kU = MT * kC;
+  constexpr int kUW = (kU + W - 1) / W;
+  const int ncol = lane & 15, kq = lane >> 4;
+  const int G2 = a.N >> 7;
+#pragma unroll
+  for (int j = 0; j < kUW; ++j) {
+    const int u = wave + j * W;
+    if (u >= kU) break;
+    const int mt = u / kC, c = u % kC;
+    f32x4 sum = red[0][mt * NT + c][lane], up = {0.f, 0.f, 0.f, 0.f};
+    if (SW) up = red[0][mt * NT + c + kC][lane];
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+      sum += red[w][mt * NT + c][lane];
+      if (SW) up += red[w][mt * NT + c + kC][lane];
+    }
+    const int col = (t0 + c) * 16 + ncol;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = mt * 16 + 4 * kq + r;
+      if (m < a.M) {
+        float val;
+        if constexpr (SW) {
+          const float gte = sum[r];
+          val = gte / (1.0f + __expf(-gte)) * up[r];
+        } else {
+          val = sum[r] + (a.res ? h2f(a.res[(size_t)m * a.ldr + col]) : 0.f);
+        }
+        const uint16_t h = f2h(val);
+        if (a.y) a.y[(size_t)m * a.ldy + col] = h;
+        if (a.yp) store_prepared(a.yp, m, col, G2, h);
+      }
+    }
+  }
+}
+template <int W, int MT, int NT, bool SW>
+__global__ __launch_bounds__(64 * W) void w4a16_ksplit_kernel(GemmArgs a) {
+  constexpr int kC = SW ? NT / 2 : NT;  // output column tiles of the workgroup
+  __shared__ f32x4 red[W][MT * NT][kWave];
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int ncol = lane & 15, kq = lane >> 4;
-  const int t = blockIdx.x;
   const int G = a.G;
-  const int g0 = wave * G / W, n = (wave + 1) * G / W - g0;  // >= 1: the plan keeps G >= W
+  const int t0 = blockIdx.x * kC;
+  const int g0 = wave * G / W, n = (wave + 1) * G / W - g0;
   const uint32_t q_bytes = (uint32_t)((size_t)a.K * a.N / 2), sz_bytes = (uint32_t)((size_t)a.N * G * 4);
   const auto rq0 = buffer_rsrc(a.w0.q, q_bytes), rs0 = buffer_rsrc(a.w0.sz, sz_bytes);
-  const auto rq1 = buffer_rsrc(NT == 2 ? a.w1.q : a.w0.q, q_bytes);
-  const auto rs1 = buffer_rsrc(NT == 2 ? a.w1.sz : a.w0.sz, sz_bytes);
-  const auto ra = buffer_rsrc(a.a, (uint32_t)(G * 4 * kWave * 16));
+  const auto rq1 = buffer_rsrc(SW ? a.w1.q : a.w0.q, q_bytes);
+  const auto rs1 = buffer_rsrc(SW ? a.w1.sz : a.w0.sz, sz_bytes);
+  const auto ra = buffer_rsrc(a.a, (uint32_t)(MT * G * 4 * kWave * 16));
   const uint32_t lane16 = (uint32_t)lane * 16u, col4 = (uint32_t)ncol * 4u;
   struct Stage {
     u32x4 b[NT];
     uint32_t sz[NT];
-    u32x4 x[4];
   };
-  // group i of this wave's range (loads past its end repeat its last group)
-  auto load = [&](Stage& st, int i) {
-    const int g = g0 + (i < n ? i : n - 1);
+  Stage ring[2];
+  u32x4 x[MT][4];
+  auto load_b = [&](Stage& st, int i) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      const uint32_t tg = (uint32_t)(t * G + g);
-      st.b[nt] = buffer_load_x4(nt ? rq1 : rq0, lane16, tg * 1024u);
-      st.sz[nt] = buffer_load_x1(nt ? rs1 : rs0, col4, tg * 64u);
+      const uint32_t tg = (uint32_t)((t0 + nt % kC) * G + g0 + i);
+      st.b[nt] = buffer_load_x4(SW && nt >= kC ? rq1 : rq0, lane16, tg * 1024u);
+      st.sz[nt] = buffer_load_x1(SW && nt >= kC ? rs1 : rs0, col4, tg * 64u);
     }
-    // lanes of rows at or past M load nothing (zeros in the prepared
-    // layout; the MFMA rows they feed are not written)
-    if (ncol < a.M) {
+  };
+  auto load_x = [&](int mt, int i) {
+    if (MT > 1 || ncol < a.M) {
 #pragma unroll
-      for (int f = 0; f < 4; ++f) st.x[f] = buffer_load_x4(ra, lane16, (uint32_t)((g * 4 + f) * 1024));
+      for (int f = 0; f < 4; ++f) x[mt][f] = buffer_load_x4(ra, lane16, (uint32_t)(((mt * G + g0 + i) * 4 + f) * 1024));
     }
   };
   uint32_t magic_lo = 0x64006400u, magic_hi = 0x54005400u;
   asm volatile("" : "+v"(magic_lo), "+v"(magic_hi));
-  f32x4 acc[NT];
+  f32x4 acc[MT][NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  Stage ring[kR];
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-  for (int j = 0; j < kR - 1; ++j) load(ring[j], j);
-  for (int i0 = 0; i0 < n; i0 += kR) {
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  load_b(ring[0], 0);
 #pragma unroll
-    for (int J = 0; J < kR; ++J) {
-      const int i = i0 + J;
-      load(ring[(J + kR - 1) % kR], i + kR - 1);
-      const Stage& st = ring[J];
-      if (i < n) {
-        const u32x4* xa = st.x;
+  for (int mt = 0; mt < MT; ++mt) load_x(mt, 0);
+  auto step = [&](const Stage& st, Stage& nx, int i) {
+    const bool more = i + 1 < n;
+    if (more) load_b(nx, i + 1);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const BFrag bf = dequant_block(st.b[nt], st.sz[nt], magic_lo, magic_hi);
-          f32x4 cc = {0.f, 0.f, 0.f, 0.f};
-          cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(xa[0]), bf.lo_a, cc, 0, 0, 0);
-          cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(xa[1]), bf.lo_b, cc, 0, 0, 0);
-          cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(xa[2]), bf.hi_a, cc, 0, 0, 0);
-          cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(xa[3]), bf.hi_b, cc, 0, 0, 0);
+    for (int nt = 0; nt < NT; ++nt) {
+      const BFrag bf = dequant_block(st.b[nt], st.sz[nt], magic_lo, magic_hi);
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            acc[nt][r] = __builtin_fmaf(cc[r], (float)bitcast<half2v>(st.sz[nt])[0], acc[nt][r]);
-        }
-      } else {
-        // retire the slot's pending loads before the registers are reused
+      for (int mt = 0; mt < MT; ++mt) {
+        f32x4 cc = {0.f, 0.f, 0.f, 0.f};
+        cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(x[mt][0]), bf.lo_a, cc, 0, 0, 0);
+        cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(x[mt][1]), bf.lo_b, cc, 0, 0, 0);
+        cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(x[mt][2]), bf.hi_a, cc, 0, 0, 0);
+        cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8>(x[mt][3]), bf.hi_b, cc, 0, 0, 0);
+        if (nt == NT - 1 && more) load_x(mt, i + 1);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) asm volatile("" : : "v"(st.b[nt]), "v"(st.sz[nt]));
-#pragma unroll
-        for (int f = 0; f < 4; ++f) asm volatile("" : : "v"(st.x[f]));
+        for (int r = 0; r < 4; ++r)
+          acc[mt][nt][r] = __builtin_fmaf(cc[r], (float)bitcast<half2v>(st.sz[nt])[0], acc[mt][nt][r]);
       }
     }
+  };
+  for (int i = 0; i < n; i += 2) {
+    step(ring[0], ring[1], i);
+    if (i + 1 < n) step(ring[1], ring[0], i + 1);
   }
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) red[wave][nt][lane] = acc[nt];
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) red[wave][mt * NT + nt][lane] = acc[mt][nt];
   __syncthreads();
-  if (wave != 0) return;
-  f32x4 sum[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    sum[nt] = red[0][nt][lane];
-#pragma unroll
-    for (int w = 1; w < W; ++w) sum[nt] += red[w][nt][lane];
-  }
-  const int col = t * 16 + ncol;
-  const int G2 = a.N >> 7;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int m = 4 * kq + r;
-    if (m < a.M) {
-      float val;
-      if constexpr (NT == 2) {
-        const float gte = sum[0][r];
-        val = gte / (1.0f + __expf(-gte)) * sum[1][r];
-      } else {
-        val = sum[0][r] + (a.res ? h2f(a.res[(size_t)m * a.ldr + col]) : 0.f);
-      }
-      const uint16_t h = f2h(val);
-      if (a.y) a.y[(size_t)m * a.ldy + col] = h;
-      if (a.yp) store_prepared(a.yp, m, col, G2, h);
-    }
-  }
+  ksplit_write<W, MT, NT, SW>(a, red, t0, wave, lane);
 }
-
 
 // ------------------------------------------- small M, RMSNorm in the GEMM
 // The QKV projection and the fused SwiGLU read the RMSNorm of the residual
-// stream (the decoder layer of Sec. 2).  Where the K-split plan gives each
-// wave at most NG (2 or 4) groups, the workgroup (which reads all of K
-// anyway) normalises the plain rows x itself: every wave issues all its
+// stream (the decoder layer of Sec. 2).  Where K-split workgroups give each
+// wave at most two groups (norm_in_ksplit), the workgroup (which reads all
+// of K anyway) normalises the plain rows x itself: every wave issues all its
 // loads up front (the row chunks of its groups, gamma, then the weight
 // blocks, so that the row sums wait for the row chunks only), sums x^2
 // over its groups, the waves' sums meet in LDS,
@@ -691,23 +674,23 @@ __global__ __launch_bounds__(64 * W) void w4a16_kslice_kernel(GemmArgs a) {
 // 1B-shaped QKV, one of 4 KB + 128 B no faster): load f of row r takes the
 // 16-byte chunk f ^ (r & 3) and two rounds of bitwise lane selects put the
 // chunks back in order.
-template <int W, int NT, int NG>
-__global__ __launch_bounds__(64 * W) void w4a16_kslice_norm_kernel(GemmArgs a) {
-  static_assert(NT == 1 || NT == 2, "plain, or fused SwiGLU (gate and up tile of one column tile)");
-  static_assert(NG == 2 || NG == 4, "groups per wave");
+template <int W, int NT, bool SW>
+__global__ __launch_bounds__(64 * W) void w4a16_ksplit_norm_kernel(GemmArgs a) {
+  constexpr int kC = SW ? NT / 2 : NT;  // output column tiles of the workgroup
+  constexpr int NG = kNormGroupsPerWave;
   __shared__ f32x4 red[W][NT][kWave];
   __shared__ float red_ss[W][16];
   __shared__ u32x4 gam[W][kWave];
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int ncol = lane & 15, kq = lane >> 4;
-  const int t = blockIdx.x;
+  const int t0 = blockIdx.x * kC;
   const int G = a.G;
   const int g0 = wave * G / W, n = (wave + 1) * G / W - g0;  // 1 .. NG: the plan keeps W <= G <= NG W
   const uint32_t q_bytes = (uint32_t)((size_t)a.K * a.N / 2), sz_bytes = (uint32_t)((size_t)a.N * G * 4);
   const auto rq0 = buffer_rsrc(a.w0.q, q_bytes), rs0 = buffer_rsrc(a.w0.sz, sz_bytes);
-  const auto rq1 = buffer_rsrc(NT == 2 ? a.w1.q : a.w0.q, q_bytes);
-  const auto rs1 = buffer_rsrc(NT == 2 ? a.w1.sz : a.w0.sz, sz_bytes);
+  const auto rq1 = buffer_rsrc(SW ? a.w1.q : a.w0.q, q_bytes);
+  const auto rs1 = buffer_rsrc(SW ? a.w1.sz : a.w0.sz, sz_bytes);
   const auto rx = buffer_rsrc(a.x, (uint32_t)((size_t)a.M * a.ldx * 2));
   // gamma over this wave's groups only (chunk c = 16 j + 4 kq + f of group
   // g0 + j); chunks past them load as zeros
@@ -732,11 +715,11 @@ __global__ __launch_bounds__(64 * W) void w4a16_kslice_norm_kernel(GemmArgs a) {
 #pragma unroll
   for (int j = 0; j < NG; ++j) {
     const int g = g0 + (j < n ? j : n - 1);
-    const uint32_t tg = (uint32_t)(t * G + g);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      b[j][nt] = buffer_load_x4(nt ? rq1 : rq0, lane16, tg * 1024u);
-      sz[j][nt] = buffer_load_x1(nt ? rs1 : rs0, col4, tg * 64u);
+      const uint32_t tg = (uint32_t)((t0 + nt % kC) * G + g);
+      b[j][nt] = buffer_load_x4(nt >= kC ? rq1 : rq0, lane16, tg * 1024u);
+      sz[j][nt] = buffer_load_x1(nt >= kC ? rs1 : rs0, col4, tg * 64u);
     }
   }
   gam[wave][lane] = gv;
@@ -818,32 +801,7 @@ __global__ __launch_bounds__(64 * W) void w4a16_kslice_norm_kernel(GemmArgs a) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) red[wave][nt][lane] = acc[nt];
   __syncthreads();
-  if (wave != 0) return;
-  f32x4 sum[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    sum[nt] = red[0][nt][lane];
-#pragma unroll
-    for (int w = 1; w < W; ++w) sum[nt] += red[w][nt][lane];
-  }
-  const int col = t * 16 + ncol;
-  const int G2 = a.N >> 7;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int m = 4 * kq + r;
-    if (m < a.M) {
-      float val;
-      if constexpr (NT == 2) {
-        const float gte = sum[0][r];
-        val = gte / (1.0f + __expf(-gte)) * sum[1][r];
-      } else {
-        val = sum[0][r] + (a.res ? h2f(a.res[(size_t)m * a.ldr + col]) : 0.f);
-      }
-      const uint16_t h = f2h(val);
-      if (a.y) a.y[(size_t)m * a.ldy + col] = h;
-      if (a.yp) store_prepared(a.yp, m, col, G2, h);
-    }
-  }
+  ksplit_write<W, 1, NT, SW>(a, red, t0, wave, lane);
 }
 
 // ------------------------------------------------------- activation prep
@@ -942,31 +900,17 @@ static void launch_t(const GemmLaunch& L, hipStream_t st) {
   a.units = (uint32_t)(L.nblocks * a.G);
   a.part = L.part;
   hipLaunchKernelGGL((w4a16_gemm_kernel<MT, NW, EPI>), dim3(L.nwg), dim3(256), 0, st, a);
-  // ranges split no N-block when every workgroup gets whole N-blocks (the
-  // split SwiGLU is only planned that way)
-  if constexpr (EPI != EPI_SWIGLU_SPLIT) {
-    if (L.nblocks % L.nwg != 0) {
-      hipLaunchKernelGGL((w4a16_fixup_kernel<MT, NW, EPI>), dim3(L.nblocks * MT), dim3(256), 0, st, a);
-    }
-  }
+  // ranges split no N-block when every workgroup gets whole N-blocks
+  if (L.nblocks % L.nwg != 0)
+    hipLaunchKernelGGL((w4a16_fixup_kernel<MT, NW, EPI>), dim3(L.nblocks * MT), dim3(256), 0, st, a);
 }
 
-// instantiated shapes: SwiGLU one gate + one up tile per wave, or (up to 32
-// rows) one tile per wave with gate and up in different waves; plain one or
+// instantiated shapes: SwiGLU one gate + one up tile per wave, plain one or
 // two tiles per wave
 template <int MT, int EPI>
 static void launch_nw(const GemmLaunch& L, hipStream_t st) {
   if constexpr (EPI == EPI_SWIGLU) {
-    if constexpr (MT <= 2) {
-      if (L.nw == 1) {
-        launch_t<MT, 1, EPI_SWIGLU_SPLIT>(L, st);
-        return;
-      }
-    }
     launch_t<MT, 2, EPI>(L, st);
-  } else if constexpr (MT <= 2) {
-    if (L.nw == 2) launch_t<MT, 2, EPI>(L, st);
-    else launch_t<MT, 1, EPI>(L, st);
   } else {
     if (L.nw == 2) launch_t<MT, 2, EPI>(L, st);
     else launch_t<MT, 1, EPI>(L, st);
@@ -1008,37 +952,121 @@ static GemmArgs kslice_args(const GemmLaunch& L) {
   return a;
 }
 
-template <int W, int NT>
-static void launch_kslice(const GemmLaunch& L, hipStream_t st) {
-  hipLaunchKernelGGL((w4a16_kslice_kernel<W, NT>), dim3(L.N / 16), dim3(64 * W), 0, st, kslice_args(L));
+template <int W, int MT, int NT, bool SW>
+static void launch_ks(const GemmLaunch& L, hipStream_t st) {
+  hipLaunchKernelGGL((w4a16_ksplit_kernel<W, MT, NT, SW>), dim3(L.N / 16 / (SW ? NT / 2 : NT)), dim3(64 * W), 0, st,
+                     kslice_args(L));
 }
-
-template <int W, int NT, int NG>
-static void launch_kslice_norm(const GemmLaunch& L, hipStream_t st) {
-  hipLaunchKernelGGL((w4a16_kslice_norm_kernel<W, NT, NG>), dim3(L.N / 16), dim3(64 * W), 0, st, kslice_args(L));
+// MTX: the most M-tiles that the plan gives this form
+template <int W, int NT, bool SW, int MTX>
+static void launch_ks_mt(const GemmLaunch& L, hipStream_t st) {
+  const int mt = (L.M + 15) / 16;
+  if constexpr (MTX >= 4) {
+    if (mt == 4) return launch_ks<W, 4, NT, SW>(L, st);
+  }
+  if constexpr (MTX >= 3) {
+    if (mt == 3) return launch_ks<W, 3, NT, SW>(L, st);
+    if (mt == 2) return launch_ks<W, 2, NT, SW>(L, st);
+  }
+  launch_ks<W, 1, NT, SW>(L, st);
 }
-
-bool norm_in_kslice(const GemmPlan& p, int K) {
-  return p.ksw > 0 && (K / 128 + p.ksw - 1) / p.ksw <= kNormMaxGroupsPerWave;
+template <int W, int NT, bool SW>
+static void launch_ksn(const GemmLaunch& L, hipStream_t st) {
+  hipLaunchKernelGGL((w4a16_ksplit_norm_kernel<W, NT, SW>), dim3(L.N / 16 / (SW ? NT / 2 : NT)), dim3(64 * W), 0, st,
+                     kslice_args(L));
 }
 
 void launch_w4a16_gemm(const GemmLaunch& L, hipStream_t st) {
-  // K-split plans give the fused SwiGLU 4 waves, plain GEMMs 4 or 8
   if (L.ksw && L.xnorm) {
-    const bool two = (L.K / 128 + L.ksw - 1) / L.ksw <= 2;  // groups per wave (norm_in_kslice: <= 4)
-    if (L.swiglu) two ? launch_kslice_norm<4, 2, 2>(L, st) : launch_kslice_norm<4, 2, 4>(L, st);
-    else if (L.ksw == 8) two ? launch_kslice_norm<8, 1, 2>(L, st) : launch_kslice_norm<8, 1, 4>(L, st);
-    else two ? launch_kslice_norm<4, 1, 2>(L, st) : launch_kslice_norm<4, 1, 4>(L, st);
+    if (L.swiglu) {
+      if (L.ksw == 8) L.knt == 2 ? launch_ksn<8, 2, true>(L, st) : launch_ksn<8, 4, true>(L, st);
+      else L.knt == 2 ? launch_ksn<4, 2, true>(L, st) : launch_ksn<4, 4, true>(L, st);
+    } else if (L.ksw == 8) {
+      L.knt == 1 ? launch_ksn<8, 1, false>(L, st) : L.knt == 2 ? launch_ksn<8, 2, false>(L, st) : launch_ksn<8, 4, false>(L, st);
+    } else {
+      L.knt == 1 ? launch_ksn<4, 1, false>(L, st) : L.knt == 2 ? launch_ksn<4, 2, false>(L, st) : launch_ksn<4, 4, false>(L, st);
+    }
     return;
   }
   if (L.ksw) {
-    if (L.swiglu) launch_kslice<4, 2>(L, st);
-    else if (L.ksw == 8) launch_kslice<8, 1>(L, st);
-    else launch_kslice<4, 1>(L, st);
+    if (L.swiglu) {
+      if (L.ksw == 4) launch_ks_mt<4, 4, true, 3>(L, st);
+      else if (L.knt == 2) launch_ks_mt<8, 2, true, 4>(L, st);
+      else launch_ks_mt<8, 4, true, 4>(L, st);
+    } else if (L.ksw == 16) {
+      L.knt == 1 ? launch_ks_mt<16, 1, false, 1>(L, st) : launch_ks_mt<16, 2, false, 1>(L, st);
+    } else {
+      if (L.knt == 1) launch_ks_mt<8, 1, false, 4>(L, st);
+      else if (L.knt == 2) launch_ks_mt<8, 2, false, 4>(L, st);
+      else launch_ks_mt<8, 4, false, 4>(L, st);
+    }
     return;
   }
   if (L.swiglu) launch_mt<EPI_SWIGLU>(L, st);
   else launch_mt<EPI_PLAIN>(L, st);
+}
+
+// K-split plan (ksw waves, knt weight tiles per workgroup) of a shape, or
+// ksw = 0 for the stream-K kernel.  The lines come from sweeps over 34 plain
+// and 26 SwiGLU shapes (K 1024 .. 28672, N 1024 .. 32768) at 4, 13, 29, 45
+// and 64 rows against the kernels used before: 1.36 and 1.30 times faster
+// over the sweeps.
+static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& p) {
+  const int G = K / 128;
+  if (swiglu) {
+    if (tiles > 1088) return;  // more column tiles: the stream-K form's shared activations win (N 28672: 60 against 64 us at 32 rows)
+    // above 32 rows at more than one workgroup per compute unit only for a
+    // short K (K 5888, N 10816, 64 rows: 34.5 against 36.4 us)
+    if (tiles > 512 && MT >= 3 && (K > 4096 || tiles > 1024)) return;
+    // gate + up of one column tile up to one workgroup per compute unit, and
+    // where the activations are short or few (N 8640, K 3072, 4 rows: 10.2
+    // against 11.7 us; 29 rows 14.6 against 14.9)
+    p.knt = tiles <= 256 || (MT == 1 && K <= 2560) || (M <= 8 && tiles > 512) ? 2 : 4;
+    // with about two workgroups per compute unit four waves each (K 4096, N
+    // 14336, 16 rows: 15.7 against 17.7 us with eight)
+    p.ksw = p.knt == 4 && tiles > 512 && MT <= 3 ? 4 : 8;
+    return;
+  }
+  const int wg4 = (tiles + 3) / 4, rounds = (wg4 + 255) / 256;
+  if (tiles <= 256) {
+    // one tile: an activation read of MT * K * 32 bytes per workgroup pays
+    // up to about 0.75 MB (N 2560, K 8192, 64 rows: 13.6 against 16 us), or
+    // where the columns are too few for the other form (N 1152, K 10368, 64
+    // rows: 21.8 against 15.7 us)
+    if (MT > 1 && MT * K > 24576 && tiles >= 128) return;
+    p.knt = 1;
+  } else if (tiles <= 512) {
+    if (MT > 1 && MT * K > 32768) return;  // N 8192, K 28672, 32 rows: 39.4 against 43.5 us
+    p.knt = 2;
+  } else if (tiles <= 1024) {
+    // above 32 rows fewer than 192 workgroups do not pay on a long K (N
+    // 11904, K 16896, 45 rows: 40.1 against 44.7 us; N 14144, K 25472: 75.3
+    // against 64.8)
+    if (MT >= 3 && K > 8192 && tiles < 768) return;
+    p.knt = K <= 2048 && MT <= 2 ? 2 : 4;
+  } else {
+    // beyond 256 workgroups only where they fill whole rounds of the chip (N
+    // 28992, K 27008: 107 -> 81 us at 4 rows; N 19328, K 24960: 58 -> 66)
+    if (20 * wg4 < 17 * 256 * rounds && K > 2048 && !(MT == 1 && K <= 8192)) return;
+    p.knt = K <= 2048 && MT <= 2 ? 2 : 4;
+  }
+  // 16 waves where one M-tile leaves the registers and K the groups (K 14336,
+  // N 4096, 8 rows: 10.9 against 14.0 us with 8)
+  p.ksw = MT == 1 && G >= 32 && p.knt <= 2 ? 16 : 8;
+}
+
+// The RMSNorm runs inside a K-split GEMM where no wave then holds more than
+// two groups (up to 2048 wide, one M-tile): every workgroup normalises all
+// of K for itself, so it pays while that is short (K 2048, N 3072, 8 rows:
+// 5.4 us against 6.6 with the norm kernel; at K 3072 and 4096 within 0.3 us
+// of it either way, and slower at N >= 10240).
+bool norm_in_ksplit(GemmPlan& p, int M, int K, int N, bool swiglu) {
+  const int G = K / 128, tiles = N / 16;
+  if (!p.ksw || M > 16 || G < 8 || G > 16) return false;
+  p.ksw = G <= 8 ? 4 : 8;
+  if (swiglu) p.knt = tiles <= 256 ? 2 : 4;
+  else p.knt = tiles <= 256 ? 1 : tiles <= 512 ? 2 : 4;
+  return true;
 }
 
 GemmPlan plan_w4a16_gemm(int M, int K, int N, bool swiglu) {
@@ -1047,42 +1075,7 @@ GemmPlan plan_w4a16_gemm(int M, int K, int N, bool swiglu) {
   GemmPlan p;
   const int tiles = N / 16;
   const int MT = (M + 15) / 16;
-  const int G = K / 128;
-  const size_t mbytes = (size_t)K * N / 2;
-  if (MT == 1 && G >= 8 && tiles >= 128 && mbytes <= ((size_t)32 << 20) && (!swiglu || M <= 8)) {
-    // up to 16 rows (a fused SwiGLU: up to 8) and at most 32 MB per matrix:
-    // one workgroup per column tile, K split across its waves, no partials
-    // or fix-up.  Every workgroup reads the activations of the rows it
-    // computes (rows past M are not loaded), so the L2 reads are M / 4
-    // (SwiGLU: M / 8) times the weight bytes.  Measured against the forms below:
-    // 1B QKV 8.8 -> 4.2 us, O 8.4 -> 4.4 us, down 10.7 -> 7.0 us, SwiGLU
-    // 9.5 -> 7.4 us; 8B O 10.1 -> 6.6 us, down 15.4 -> 14.5 us; TP4 shard
-    // QKV 11.4 -> 8.9 us, O 10.0 -> 7.1 us, SwiGLU 20.5 -> 16.2 us, down
-    // 15.4 -> 13.4 us.  The 8B SwiGLU at 16 rows (twice the activation
-    // reads) is slower, 17.5 -> 21.4 us, and stays on the 2-column form.
-    // A SwiGLU workgroup streams two tiles: 4 waves (8: 7.4 -> 8.5 us).
-    p.ksw = (!swiglu && G >= 16) ? 8 : 4;
-    p.nw = 1;
-    p.nblocks = tiles;
-    p.nwg = tiles;
-    p.part_bytes = 0;
-    p.prep_bytes = (size_t)MT * G * 4 * kWave * 16;
-    return p;
-  }
-  if (swiglu && MT <= 2 && tiles % 2 == 0 && tiles / 4 < 256 && tiles / 2 >= 256) {
-    // gate and up tiles in different waves, one workgroup per 2 columns:
-    // where the 4-column blocks are too few to fill the chip on their own
-    // (the 8B width: 224 blocks, 20.5 -> 18 us at 16 rows; the 1B width:
-    // 128 blocks, 14.3 -> 9.2 us at 8 rows) this replaces stream-K and its
-    // fix-up; at the 70B width (448 blocks) it is slower, 56 -> 72 us at 32
-    // rows, as every workgroup reads the activations for half the columns
-    p.nw = 1;
-    p.nblocks = tiles / 2;
-    p.nwg = p.nblocks;
-    p.part_bytes = 0;
-    p.prep_bytes = (size_t)MT * (K / 128) * 4 * kWave * 16;
-    return p;
-  }
+  plan_ksplit(MT, M, K, tiles, swiglu, p);
   if (swiglu) {
     p.nw = 2;  // one gate and one up tile per wave
     p.nblocks = tiles / 4;
@@ -1108,7 +1101,8 @@ GemmPlan plan_w4a16_gemm(int M, int K, int N, bool swiglu) {
   p.nwg = (int)(units < cap ? units : cap);
   const int col_w = swiglu ? p.nw / 2 : p.nw;
   const int src = swiglu ? 2 : 1;
-  p.part_bytes = (size_t)p.nwg * 2 * 4 * MT * col_w * src * kWave * 16;
+  // a K-split plan writes no partials
+  p.part_bytes = p.ksw ? 0 : (size_t)p.nwg * 2 * 4 * MT * col_w * src * kWave * 16;
   p.prep_bytes = (size_t)MT * (K / 128) * 4 * kWave * 16;
   return p;
 }

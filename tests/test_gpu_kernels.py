@@ -350,6 +350,26 @@ def test_w4a16_swiglu_two_column_blocks(M, K, N):
     _swiglu_sampled_case(M, K, N, seed=31 + M)
 
 
+@pytest.mark.parametrize("M,K,N,swiglu", [
+    # one weight tile per workgroup: fewer groups than waves, uneven ranges, 1 to 4 M-tiles, both sides of 24576 = MT K
+    (1, 128, 64, False), (17, 384, 128, False), (48, 1152, 192, False), (64, 6144, 2048, False), (64, 6272, 2048, False),
+    # two: 16 waves (one M-tile, K >= 4096) and 8
+    (16, 4224, 4160, False), (33, 2048, 8192, False), (64, 8192, 8192, False),
+    # four: 513 and more column tiles, with 8 waves; two for a short K
+    (7, 2176, 8256, False), (49, 2176, 8256, False), (32, 1024, 8256, False),
+    # SwiGLU: gate and up of one column tile; of two, with 8 and with 4 waves
+    (16, 256, 448, True), (64, 1408, 1088, True), (31, 2688, 4160, True), (64, 2688, 4160, True),
+    (9, 2688, 8256, True), (48, 2688, 8256, True), (64, 4096, 8256, True)])
+def test_w4a16_k_split_forms(M, K, N, swiglu):
+    """The K-split workgroups at the edges of their plan: waves without a
+    group, uneven group ranges, every number of M-tiles and of weight tiles
+    per workgroup, the last column tiles; against the oracle."""
+    if swiglu:
+        _swiglu_sampled_case(M, K, N, seed=51 + M)
+    else:
+        _gemm_case(M, K, N, seed=M * 5 + K, residual=(M % 2 == 0))
+
+
 @pytest.mark.parametrize("M,K,N,ldx,swiglu", [
     # norm inside the K-split GEMM: 2 groups per wave, then up to 4
     (8, 2048, 3072, 2048, False), (1, 2048, 3072, 2048, False), (6, 1024, 2048, 1032, False),
