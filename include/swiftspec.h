@@ -35,9 +35,9 @@
  *   - Scratch memory is a caller-provided device workspace whose size comes
  *     from the matching *_workspace_bytes query.  The first
  *     SWIFTSPEC_WS_HEADER_BYTES bytes of every workspace hold an error word
- *     and ticket counters that must be zero before first use (allocate it
+ *     and reserved words that must be zero before first use (allocate it
  *     zero-filled or call swiftspec_workspace_init once); every call leaves
- *     them zero again.  Calls sharing one workspace must not overlap in
+ *     the reserved words zero.  Calls sharing one workspace must not overlap in
  *     time (use one stream per workspace).
  *   - Per-step data that lives in device memory (prefix length, parent
  *     array, accepted node) is validated on the device: an invalid value
@@ -332,8 +332,7 @@ int swiftspec_kv_reorganize(uint16_t* k_cache, uint16_t* v_cache, int32_t n_laye
  * device), in decreasing order.  Logits are expected to be finite.
  * 1 <= n <= 64, 1 <= k <= 8, k <= V, ldl >= V, ldl % 8 == 0, logits 16-byte
  * aligned.  ws: swiftspec_topk_logprobs_workspace_bytes(n) bytes (per-range
- * partial lists after the header; the header's counters are used and left
- * zero). */
+ * partial lists after the header). */
 size_t swiftspec_topk_logprobs_workspace_bytes(int32_t n);
 int swiftspec_topk_logprobs(const uint16_t* logits, int32_t ldl, int32_t n, int32_t V, int32_t k,
                             int32_t* d_tokens, float* d_logprobs, void* ws, size_t ws_bytes, void* stream);
@@ -434,8 +433,7 @@ int swiftspec_draft_tree_reroot(swiftspec_draft_tree* t, const int32_t* verified
  * same stream, so verify, accept and commit replay as one graph.
  * 1 <= T <= 64, ldl >= V, ldl % 8 == 0, logits 16-byte aligned.  ws: a
  * workspace of swiftspec_greedy_accept_workspace_bytes(T) bytes (per-range
- * partial maxima after the header; the header's first ticket counter is
- * used and left zero).  An invalid tree sets SWIFTSPEC_DEVERR_BAD_TREE;
+ * partial maxima after the header).  An invalid tree sets SWIFTSPEC_DEVERR_BAD_TREE;
  * d_argmax is still written, the other outputs are not. */
 size_t swiftspec_greedy_accept_workspace_bytes(int32_t T);
 int swiftspec_greedy_accept(const uint16_t* logits, int32_t ldl, int32_t T, int32_t V,

@@ -2,23 +2,28 @@
 // tree expansion): per logits row, the k most probable tokens and their
 // log-softmax values.
 //
-// Each row [V] fp16 is split into S contiguous ranges of 16-byte vectors,
-// one 256-thread workgroup each (S = 1024 / n, at most 64: about one vector
-// per thread at a 128256-entry vocabulary).  Entries are 64-bit sort keys
-// (order-preserving logit bits above the inverted index), so a comparison
-// of (value, index) pairs is one unsigned compare.  A thread keeps
+// Two kernels.  The first splits each row [V] fp16 into S contiguous ranges of
+// 16-byte vectors, one 256-thread workgroup each (S = 1024 / n, at most 64:
+// about one vector per thread at a 128256-entry vocabulary).  Entries are sort
+// keys: order-preserving logit bits above the inverted index, so a comparison
+// of (value, index) pairs is one unsigned compare.  Inside a range of up to
+// 65536 columns the index is the one in the range and a key has 32 bits (a
+// compare-exchange is a maximum and a minimum); wider ranges and the second
+// kernel use 64-bit keys with the column itself.  A thread keeps
 //   - a descending list of its kTopK best keys (each vector's 8 keys sorted
 //     by a bitonic network and merged in), and
-//   - an online softmax normaliser (m, s): s = sum exp(x - m) over its
-//     values, rescaled whenever m grows.
-// Lists and normalisers are merged by butterflies across lanes (bitonic
-// merge of two sorted lists per step, all of a step's shuffles independent):
-// the wave's 64, then the workgroup's 4 in wave 0, whose lanes publish the
-// list and normaliser to workspace slots with agent-scope stores; the last
-// workgroup of a row to draw a ticket merges the row's S slots the same way
-// (lane = range) and writes token and x - m - log(s) for the first k
-// entries.  Merges follow fixed patterns, so results do not depend on
-// arrival order.
+//   - a softmax normaliser (m, s): s = sum exp(x - m) over its values, m its
+//     largest, rescaled once per vector whose largest value grows m.
+// Lists and normalisers are merged by butterflies across lanes (bitonic merge
+// of two sorted lists per step; partners by DPP and permlane swaps, which cost
+// a few cycles where an LDS permute costs over a hundred): the wave's 64, then
+// the workgroup's 4 in wave 0, which writes the list and normaliser to a
+// workspace slot.  The second kernel, a wave per row (lane = range), merges the
+// row's S slots the same way and writes token and x - m - log(s) for the first
+// k entries.  Merges follow fixed patterns, so results do not depend on
+// arrival order.  w = 8, V = 128256: 5.8 + 4.7 us
+// against 18.9 us as one kernel with 64-bit keys, LDS permutes and a ticket per
+// workgroup (called eagerly 18.2 -> 10.6 us).
 #include "ss_device.h"
 #include "ss_internal.h"
 
@@ -33,20 +38,30 @@ struct TopkArgs {
   int32_t* tokens;
   float* logprobs;
   void* ws;
-  uint64_t* part;   // [n][S][kTopK] sort keys
+  uint64_t* part;   // [n][kTopK][S] sort keys
   uint64_t* stats;  // [n][S] (s bits << 32 | m bits)
 };
 
-// Sort key of (fp16 logit h, index): a larger key is a larger logit, or an
-// equal logit at a lower index.  The logit's 16 bits are made order-
-// preserving (negative values inverted, non-negative ones offset by the
-// sign bit, -0 taken as +0); the index is stored inverted below them.
-// Key 0 lies below every finite logit and marks an empty entry.
-__device__ __forceinline__ uint64_t make_key(uint32_t h, int idx) {
-  uint32_t o = (h & 0x8000u) ? (~h & 0xFFFFu) : (h | 0x8000u);
-  if (h == 0x8000u) o = 0x8000u;
-  return ((uint64_t)o << 32) | (0xFFFFFFFFu - (uint32_t)idx);
+// The logit's 16 bits made order-preserving (negative values inverted,
+// non-negative ones offset by the sign bit, -0 taken as +0), so that a larger
+// key is a larger logit, or an equal logit at a lower index (stored inverted
+// below it).  Key 0 lies below every finite logit and marks an empty entry.
+__device__ __forceinline__ uint32_t ordered(uint32_t h) {
+  const uint32_t o = (h & 0x8000u) ? (~h & 0xFFFFu) : (h | 0x8000u);
+  return h == 0x8000u ? 0x8000u : o;
 }
+// inside a range: the index in the range, up to 65535
+__device__ __forceinline__ void make_key(uint32_t& key, uint32_t h, int, int in_range) {
+  key = (ordered(h) << 16) | (0xFFFFu - (uint32_t)in_range);
+}
+__device__ __forceinline__ void make_key(uint64_t& key, uint32_t h, int idx, int) {
+  key = ((uint64_t)ordered(h) << 32) | (0xFFFFFFFFu - (uint32_t)idx);
+}
+// a range's key with its column (first: the range's first column)
+__device__ __forceinline__ uint64_t global_key(uint32_t key, int first) {
+  return key ? ((uint64_t)(key >> 16) << 32) | (0xFFFFFFFFu - (uint32_t)(first + (int)(0xFFFFu - (key & 0xFFFFu)))) : 0ull;
+}
+__device__ __forceinline__ uint64_t global_key(uint64_t key, int) { return key; }
 __device__ __forceinline__ float key_value(uint64_t key) {
   const uint32_t o = (uint32_t)(key >> 32);
   return h2f((uint16_t)((o & 0x8000u) ? (o & 0x7FFFu) : (~o & 0xFFFFu)));
@@ -54,8 +69,9 @@ __device__ __forceinline__ float key_value(uint64_t key) {
 __device__ __forceinline__ int key_index(uint64_t key) { return (int)(0xFFFFFFFFu - (uint32_t)key); }
 
 // compare-exchange: afterwards a >= b
-__device__ __forceinline__ void cmpx(uint64_t& a, uint64_t& b) {
-  const uint64_t hi = a > b ? a : b, lo = a > b ? b : a;
+template <class Key>
+__device__ __forceinline__ void cmpx(Key& a, Key& b) {
+  const Key hi = a > b ? a : b, lo = a > b ? b : a;
   a = hi;
   b = lo;
 }
@@ -63,7 +79,8 @@ __device__ __forceinline__ void cmpx(uint64_t& a, uint64_t& b) {
 // The kTopK best of two descending lists: the elementwise larger of `a` and
 // reversed `b` is bitonic and holds exactly that set; three half-cleaner
 // stages sort it.  Result in `a`.
-__device__ __forceinline__ void merge_top(uint64_t (&a)[kTopK], const uint64_t (&b)[kTopK]) {
+template <class Key>
+__device__ __forceinline__ void merge_top(Key (&a)[kTopK], const Key (&b)[kTopK]) {
 #pragma unroll
   for (int j = 0; j < kTopK; ++j) a[j] = a[j] > b[kTopK - 1 - j] ? a[j] : b[kTopK - 1 - j];
 #pragma unroll
@@ -74,7 +91,8 @@ __device__ __forceinline__ void merge_top(uint64_t (&a)[kTopK], const uint64_t (
 }
 
 // Bitonic sorting network, descending.
-__device__ __forceinline__ void sort_desc(uint64_t (&a)[kTopK]) {
+template <class Key>
+__device__ __forceinline__ void sort_desc(Key (&a)[kTopK]) {
 #pragma unroll
   for (int k = 2; k <= kTopK; k <<= 1)
 #pragma unroll
@@ -105,43 +123,57 @@ __device__ __forceinline__ void lse_combine_into(float& m, float& s, float m2, f
   m = mm;
 }
 
-// Butterfly over groups of `width` lanes (a power of two up to 64): after
-// step `off` each lane holds the kTopK best of its own and lane ^ off's
-// lists, and the combined normaliser.  Every lane of a group ends with the
-// group's list and normaliser.
-__device__ __forceinline__ void butterfly_merge(uint64_t (&L)[kTopK], float& m, float& s, int width) {
-  for (int off = 1; off < width; off <<= 1) {
-    uint64_t o[kTopK];
-#pragma unroll
-    for (int j = 0; j < kTopK; ++j) o[j] = shfl_u64(L[j], lane_id() ^ off);
-    const float om = __shfl_xor(m, off, kWave), os = __shfl_xor(s, off, kWave);
-    merge_top(L, o);
-    if (lane_id() & off) lse_combine_into(m, s, om, os);
-    else lse_combine(m, s, om, os);
+// Step STEP of a butterfly over the lanes: the value of a lane whose bit STEP
+// differs and which lies in the same group of 2^(STEP + 1) (steps 2 and 3
+// mirror the group: every lane of the other half holds the same list by then).
+template <int STEP>
+__device__ __forceinline__ uint32_t partner(uint32_t x) {
+  if constexpr (STEP < 4) {
+    constexpr int kCtrl = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : STEP == 2 ? 0x141 : 0x140;  // quad_perm, half and row mirror
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, 0xF, 0xF, true);
+  } else {
+    uint32_t lo = x, hi = x;  // after the swap the even and the odd halves of x, each held by both
+    if constexpr (STEP == 4) asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(lo), "+v"(hi));
+    else asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(lo), "+v"(hi));
+    return (lane_id() >> STEP) & 1 ? lo : hi;
   }
 }
+template <int STEP>
+__device__ __forceinline__ uint64_t partner(uint64_t x) {
+  return ((uint64_t)partner<STEP>((uint32_t)(x >> 32)) << 32) | partner<STEP>((uint32_t)x);
+}
+template <int STEP>
+__device__ __forceinline__ float partner(float x) {
+  return __uint_as_float(partner<STEP>(__float_as_uint(x)));
+}
 
-__global__ __launch_bounds__(256) void topk_logprobs_kernel(TopkArgs a) {
-  __shared__ uint64_t s_key[4][kTopK];
+// Butterfly steps FIRST .. LAST: after them each lane of a group of 2^(LAST+1)
+// holds the kTopK best of the group's lists and the combined normaliser.
+template <int STEP, int LAST, class Key>
+__device__ __forceinline__ void butterfly_merge(Key (&L)[kTopK], float& m, float& s) {
+  Key o[kTopK];
+#pragma unroll
+  for (int j = 0; j < kTopK; ++j) o[j] = partner<STEP>(L[j]);
+  const float om = partner<STEP>(m), os = partner<STEP>(s);
+  merge_top(L, o);
+  if ((lane_id() >> STEP) & 1) lse_combine_into(m, s, om, os);
+  else lse_combine(m, s, om, os);
+  if constexpr (STEP < LAST) butterfly_merge<STEP + 1, LAST>(L, m, s);
+}
+
+template <class Key>
+__global__ __launch_bounds__(256) void topk_ranges_kernel(TopkArgs a) {
+  __shared__ Key s_key[4][kTopK];
   __shared__ float s_m[4], s_s[4];
-  __shared__ int s_last;
   const int row = blockIdx.x / a.S, sp = blockIdx.x % a.S;
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = tid >> 6;
   const uint16_t* x = a.logits + (size_t)row * a.ldl;
-  uint64_t L[kTopK];
+  Key L[kTopK];
 #pragma unroll
   for (int j = 0; j < kTopK; ++j) L[j] = 0;
   float m = -INFINITY, s = 0.f;
-  auto stat = [&](float v) {
-    if (v > m) {
-      s = s * __expf(m - v) + 1.0f;
-      m = v;
-    } else {
-      s += __expf(v - m);
-    }
-  };
   const int nvec = a.V >> 3;
   const int j_lo = min(nvec, sp * a.chunk), j_hi = min(nvec, j_lo + a.chunk);
   for (int j0 = j_lo + tid; j0 < j_hi; j0 += 256 * kExpandVecs) {
@@ -156,31 +188,45 @@ __global__ __launch_bounds__(256) void topk_logprobs_kernel(TopkArgs a) {
       const int j = j0 + 256 * u;
       if (j >= j_hi) break;
       // one vector: its 8 keys sorted, then merged into the running list
-      uint64_t c[kTopK];
+      Key c[kTopK];
+      float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const uint32_t h = (w[u][e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-        c[e] = make_key(h, 8 * j + e);
-        stat(h2f((uint16_t)h));
+        make_key(c[e], h, 8 * j + e, 8 * (j - j_lo) + e);
+        v[e] = h2f((uint16_t)h);
+      }
+      float mv = fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7])));
+      if (mv > m) {
+        s *= __expf(m - mv);
+        m = mv;
+      }
+      // (a vector of -inf alone leaves m and adds nothing)
+      if (m > -INFINITY) {
+        float sv = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sv += __expf(v[e] - m);
+        s += sv;
       }
       sort_desc(c);
       merge_top(L, c);
     }
   }
   if (sp == a.S - 1) {  // the columns past the last whole vector (fewer than 8)
-    uint64_t c[kTopK];
+    Key c[kTopK];
 #pragma unroll
     for (int e = 0; e < kTopK; ++e) c[e] = 0;
     const int i = 8 * nvec + tid;
     if (i < a.V) {
-      c[0] = make_key(x[i], i);
-      stat(h2f(x[i]));
+      make_key(c[0], x[i], i, i - 8 * j_lo);
+      const float v = h2f(x[i]);
+      lse_combine(m, s, v, 1.0f);
     }
     merge_top(L, c);
   }
 
   // the wave's list and normaliser (every lane), then the workgroup's in wave 0
-  butterfly_merge(L, m, s, kWave);
+  butterfly_merge<0, 5>(L, m, s);
   if (lane == 0) {
 #pragma unroll
     for (int r = 0; r < kTopK; ++r) s_key[wave][r] = L[r];
@@ -188,50 +234,32 @@ __global__ __launch_bounds__(256) void topk_logprobs_kernel(TopkArgs a) {
     s_s[wave] = s;
   }
   __syncthreads();
-  if (wave == 0) {
-    uint64_t W[kTopK];
-    float wm = -INFINITY, wsum = 0.f;
+  if (wave != 0) return;
 #pragma unroll
-    for (int r = 0; r < kTopK; ++r) W[r] = lane < 4 ? s_key[lane & 3][r] : 0;
-    if (lane < 4) {
-      wm = s_m[lane];
-      wsum = s_s[lane];
-    }
-    butterfly_merge(W, wm, wsum, 16);  // lanes 0..15 (4..15 empty) all end with the result
-    // lane 0 (which holds the whole list, like every lane) publishes the
-    // entries and the normaliser and takes the ticket, so that the ticket's
-    // release covers every store of the partial
-    if (lane == 0) {
-      const size_t slot = (size_t)row * a.S + sp;
+  for (int r = 0; r < kTopK; ++r) L[r] = s_key[lane & 3][r];
+  m = s_m[lane & 3];
+  s = s_s[lane & 3];
+  butterfly_merge<0, 1>(L, m, s);  // every group of four lanes holds the four waves
+  Key mine = L[0];
 #pragma unroll
-      for (int r = 0; r < kTopK; ++r)
-        __hip_atomic_store(a.part + slot * kTopK + r, W[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(a.stats + slot, ((uint64_t)__float_as_uint(wsum) << 32) | __float_as_uint(wm),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      uint32_t* row_counter = ws_counters(a.ws) + 16 * (1 + row);  // 64 bytes apart
-      const bool last = take_ticket(row_counter) == (uint32_t)(a.S - 1);
-      if (last) reset_counter(row_counter);  // for the next launch (stream-ordered)
-      s_last = last;
-    }
-  }
-  __syncthreads();
-  if (!s_last || wave != 0) return;
+  for (int r = 1; r < kTopK; ++r)
+    if (lane == r) mine = L[r];
+  if (lane < kTopK) a.part[((size_t)row * kTopK + lane) * a.S + sp] = global_key(mine, 8 * j_lo);
+  if (lane == kTopK) a.stats[(size_t)row * a.S + sp] = ((uint64_t)__float_as_uint(s) << 32) | __float_as_uint(m);
+}
 
-  // ---- the row's last workgroup, one wave: lane q holds range q ----
+__global__ __launch_bounds__(64) void topk_rows_kernel(TopkArgs a) {
+  const int row = blockIdx.x, lane = lane_id();
   uint64_t R[kTopK];
   float rm = -INFINITY, rs = 0.f;
 #pragma unroll
-  for (int r = 0; r < kTopK; ++r)
-    R[r] = lane < a.S ? __hip_atomic_load(a.part + ((size_t)row * a.S + lane) * kTopK + r, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT)
-                      : 0;
+  for (int r = 0; r < kTopK; ++r) R[r] = lane < a.S ? a.part[((size_t)row * kTopK + r) * a.S + lane] : 0;
   if (lane < a.S) {
-    const uint64_t st = __hip_atomic_load(a.stats + (size_t)row * a.S + lane, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t st = a.stats[(size_t)row * a.S + lane];
     rm = __uint_as_float((uint32_t)st);
     rs = __uint_as_float((uint32_t)(st >> 32));
   }
-  butterfly_merge(R, rm, rs, kWave);
+  butterfly_merge<0, 5>(R, rm, rs);
   const float lse = rm + __logf(rs);
   if (lane < a.k) {
     uint64_t key = R[0];
@@ -258,7 +286,10 @@ void launch_topk_logprobs(const uint16_t* logits, int ldl, int n, int V, int k, 
   const int nvec = V >> 3;
   uint64_t* p = reinterpret_cast<uint64_t*>(part);
   TopkArgs a{logits, ldl, n, V, k, S, (nvec + S - 1) / S, tokens, logprobs, ws, p, p + (size_t)n * S * kTopK};
-  hipLaunchKernelGGL(topk_logprobs_kernel, dim3(n * S), dim3(256), 0, st, a);
+  // an index in a range fits 16 bits (the last range holds up to 7 columns more)
+  if ((size_t)a.chunk * 8 + 8 <= 65536) hipLaunchKernelGGL(topk_ranges_kernel<uint32_t>, dim3(n * S), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(topk_ranges_kernel<uint64_t>, dim3(n * S), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(topk_rows_kernel, dim3(n), dim3(64), 0, st, a);
 }
 
 }  // namespace ss

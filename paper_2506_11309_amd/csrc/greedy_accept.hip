@@ -4,24 +4,24 @@
 // where each iteration's output is the accepted root path followed by one
 // token the target produced after it).
 //
-// Each logits row [V] fp16 is split into S contiguous ranges of 16-byte
-// vectors, one 256-thread workgroup each (S = 1024 / T: about a thousand
-// workgroups for any tree size; 8 loads in flight per thread).  A thread
-// keeps (value, index) over increasing indices; the wave and the workgroup
-// combine pairs (larger value; on equal values the lower index), and the
-// pair goes to a workspace slot with an agent-scope store.  Tickets come in
-// two levels: the workgroup that draws the last ticket of its row combines
-// the row's S pairs in range order (agent-scope loads, so every slot is
-// visible whichever XCD wrote it), which gives the first index of the row's
-// largest value -- the target's choice after that node -- and takes a ticket
-// on the step's counter; the last row to finish walks the tree in one
-// wavefront (lane = node): from the root, the next node is the lowest-index
-// child whose draft token equals the current node's choice (one ballot per
-// step, at most T - 1 steps, each to a higher index), and the node where no
-// child matches is accepted; its choice is the bonus token.  At the
-// 80-layer shape (T = 64, V = 128256): 10.5 us; one workgroup per row took
-// 41 us and a single counter for all 1024 workgroups 19.6 us (the atomics on
-// one address serialise).
+// Two kernels.  The first splits each logits row [V] fp16 into S contiguous
+// ranges of 16-byte vectors, one 256-thread workgroup each (S = 1024 / T: about
+// a thousand workgroups for any tree size; 8 loads in flight per thread).  A
+// thread keeps (value, index) over increasing indices; the wave and the
+// workgroup combine pairs (larger value; on equal values the lower index), and
+// the pair goes to a workspace slot.  The second, one workgroup, combines every
+// row's S pairs (2^ceil(log2 S) lanes a row), which gives the first index of the
+// row's largest value -- the target's choice after that node -- and then walks
+// the tree in one wavefront (lane = node): from the root, the next node is the
+// lowest-index child whose draft token equals the current node's choice (one
+// ballot per step, at most T - 1 steps, each to a higher index), and the node
+// where no child matches is accepted; its choice is the bonus token.
+//
+// The kernel boundary is what makes the pairs visible: one kernel whose last
+// workgroup (tickets with acquire-release at agent scope) did the second part
+// spent most of its time on the tickets' cache writebacks, one per workgroup.
+// T = 64, V = 128256 (16.4 MB, from the Infinity Cache): 26.2 us as one kernel,
+// 7.7 + 3.9 us as two.
 #include "ss_device.h"
 #include "ss_internal.h"
 
@@ -38,6 +38,7 @@ struct AcceptArgs {
   int32_t* path_len;
   void* ws;
   uint64_t* part;  // [T][S] (index << 32 | value bits) per workgroup
+  int lanes;       // lanes that combine a row in the second kernel: the power of two from S up
 };
 
 // (v, i) beats (bv, bi): larger value, or equal value at a lower index
@@ -45,10 +46,9 @@ __device__ __forceinline__ bool beats(float v, int i, float bv, int bi) { return
 
 constexpr int kAcceptVecs = 8;  // 16-byte loads in flight per thread
 
-__global__ __launch_bounds__(256) void greedy_accept_kernel(AcceptArgs a) {
+__global__ __launch_bounds__(256) void row_argmax_kernel(AcceptArgs a) {
   __shared__ float s_v[4];
   __shared__ int s_i[4];
-  __shared__ int s_ticket;
   const int row = blockIdx.x / a.S, sp = blockIdx.x % a.S;
   const int tid = threadIdx.x;
   const int lane = lane_id();
@@ -109,48 +109,52 @@ __global__ __launch_bounds__(256) void greedy_accept_kernel(AcceptArgs a) {
         bv = s_v[w];
         bi = s_i[w];
       }
-    __hip_atomic_store(a.part + blockIdx.x, ((uint64_t)(uint32_t)bi << 32) | __float_as_uint(bv), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    // tickets in two levels, so that no counter takes more than max(S, T)
-    // atomics: the last workgroup of a row combines the row, the last row
-    // to finish walks the tree
-    uint32_t* row_counter = ws_counters(a.ws) + 16 * (1 + row);  // 64 bytes apart
-    int last = 0;
-    if (take_ticket(row_counter) == (uint32_t)(a.S - 1)) {
-      reset_counter(row_counter);
-      float cv = -INFINITY;
-      int ci = a.V;
-      for (int q = 0; q < a.S; ++q) {  // the row's ranges in order
-        const uint64_t pq =
-            __hip_atomic_load(a.part + (size_t)row * a.S + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float v = __uint_as_float((uint32_t)pq);
-        const int i = (int)(pq >> 32);
-        if (beats(v, i, cv, ci)) {
-          cv = v;
-          ci = i;
-        }
-      }
-      // a row of NaNs alone keeps the sentinel: report index 0
-      __hip_atomic_store(a.argmax + row, ci < a.V ? ci : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = take_ticket(ws_counters(a.ws)) == (uint32_t)(a.T - 1);
+    a.part[blockIdx.x] = ((uint64_t)(uint32_t)bi << 32) | __float_as_uint(bv);
+  }
+}
+
+__global__ __launch_bounds__(1024) void greedy_accept_kernel(AcceptArgs a) {
+  __shared__ int s_choice[64];
+  const int tid = threadIdx.x;
+  const int lane = lane_id();
+  // the tree and its tokens, needed by wave 0 at the end, in flight first
+  const bool in = tid < a.T;
+  const int p = in ? a.parent[tid] : -1;
+  const int tok = in ? a.tokens[tid] : 0;
+  const int q = tid & (a.lanes - 1);
+  for (int r0 = 0; r0 < a.T; r0 += 1024 / a.lanes) {
+    const int row = r0 + tid / a.lanes;
+    float cv = -INFINITY;
+    int ci = a.V;
+    if (row < a.T && q < a.S) {
+      const uint64_t pq = a.part[(size_t)row * a.S + q];
+      cv = __uint_as_float((uint32_t)pq);
+      ci = (int)(pq >> 32);
     }
-    s_ticket = last;
+    for (int off = a.lanes >> 1; off >= 1; off >>= 1) {
+      const float ov = __shfl_xor(cv, off, kWave);
+      const int oi = __shfl_xor(ci, off, kWave);
+      if (beats(ov, oi, cv, ci)) {
+        cv = ov;
+        ci = oi;
+      }
+    }
+    if (row < a.T && q == 0) {
+      const int c = ci < a.V ? ci : 0;  // a row of NaNs alone keeps the sentinel: report index 0
+      a.argmax[row] = c;
+      s_choice[row] = c;
+    }
   }
   __syncthreads();
-  if (!s_ticket || wave != 0) return;
+  if (tid >= kWave) return;
 
-  // ---- the last row to finish, one wavefront (lane = node): validate the
-  // tree and walk it ----
-  if (lane == 0) reset_counter(ws_counters(a.ws));  // for the next launch (stream-ordered)
-  const bool in = lane < a.T;
-  const int choice = in ? __hip_atomic_load(a.argmax + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-  const int p = in ? a.parent[lane] : -1;
+  // ---- one wavefront (lane = node): validate the tree and walk it ----
+  const int choice = in ? s_choice[lane] : 0;
   const bool ok = !in || (lane == 0 ? p == -1 : (p >= 0 && p < lane));
   if (!__all(ok)) {
     if (lane == 0) report_error(a.ws, SWIFTSPEC_DEVERR_BAD_TREE);
     return;
   }
-  const int tok = in ? a.tokens[lane] : 0;
   int u = 0, L = 1;
   for (int step = 1; step < a.T; ++step) {  // each step moves to a higher index: at most T - 1
     const int want = __shfl(choice, u, kWave);
@@ -178,8 +182,10 @@ void launch_greedy_accept(const uint16_t* logits, int ldl, int T, int V, const i
   const int S = greedy_accept_splits(T);
   const int nvec = V >> 3;
   AcceptArgs a{logits, ldl, T, V, S, (nvec + S - 1) / S, tokens, parent, argmax, accepted, bonus, path_len, ws,
-               reinterpret_cast<uint64_t*>(part)};
-  hipLaunchKernelGGL(greedy_accept_kernel, dim3(T * S), dim3(256), 0, st, a);
+               reinterpret_cast<uint64_t*>(part), 1};
+  while (a.lanes < S) a.lanes *= 2;
+  hipLaunchKernelGGL(row_argmax_kernel, dim3(T * S), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(greedy_accept_kernel, dim3(1), dim3(1024), 0, st, a);
 }
 
 }  // namespace ss

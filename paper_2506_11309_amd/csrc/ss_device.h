@@ -17,16 +17,8 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
 
-// Workspace header: error word at byte 0, ticket counters from byte 256.
-constexpr uint32_t kWsHeaderBytes = 65536u;
-constexpr uint32_t kWsCounterOffset = 256u;
-constexpr uint32_t kWsMaxCounters = (kWsHeaderBytes - kWsCounterOffset) / 4u;
-
+// Workspace header: error word at byte 0.
 __device__ __forceinline__ uint32_t* ws_error_word(void* ws) { return reinterpret_cast<uint32_t*>(ws); }
-__device__ __forceinline__ uint32_t* ws_counters(void* ws) {
-  return reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + kWsCounterOffset);
-}
-
 __device__ __forceinline__ void report_error(void* ws, uint32_t bits) {
   if (ws) __hip_atomic_fetch_or(ws_error_word(ws), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -103,24 +95,6 @@ __device__ __forceinline__ V bitcast(const S& s) {
   return v;
 }
 
-// Agent-scope (cross-XCD) coherent 8-byte store / load for split partials.
-__device__ __forceinline__ void store_agent_u64(void* p, uint64_t v) {
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t load_agent_u64(const void* p) {
-  return __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void store_agent_f32x4(float* p, f32x4 v) {
-  store_agent_u64(p, bitcast<uint64_t>(f32x2{v[0], v[1]}));
-  store_agent_u64(p + 2, bitcast<uint64_t>(f32x2{v[2], v[3]}));
-}
-__device__ __forceinline__ f32x4 load_agent_f32x4(const float* p) {
-  f32x2 a = bitcast<f32x2>(load_agent_u64(p));
-  f32x2 b = bitcast<f32x2>(load_agent_u64(p + 2));
-  return f32x4{a[0], a[1], b[0], b[1]};
-}
-
 // Workgroup barrier without a memory fence: s_barrier after the wave's own
 // LDS traffic has completed.  __syncthreads() would also wait for every
 // outstanding global load (prefetched tiles); the empty asm statements
@@ -173,19 +147,6 @@ template <int N>
 __device__ __forceinline__ void vm_wait() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-// Ticket for the deterministic "last arriving workgroup combines" pattern,
-// taken by the lane that stored the workgroup's partial.  Acquire-release at
-// agent scope: the release publishes that lane's earlier stores (every
-// later ticket holder reads the counter through the release sequence of
-// these read-modify-writes), and the acquire lets the last holder read
-// every earlier holder's stores; other lanes of the last workgroup read
-// them after a workgroup barrier that follows the ticket.
-__device__ __forceinline__ uint32_t take_ticket(uint32_t* counter) {
-  return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void reset_counter(uint32_t* counter) {
-  __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace ss

@@ -74,6 +74,18 @@ def test_greedy_accept_matches_oracle(T, V, pad):
     assert ss.read_device_error(ws) == 0
 
 
+@pytest.mark.parametrize("T,V", [(2, 70000), (15, 3001), (16, 4096), (33, 9000), (45, 20011), (63, 511)])
+def test_greedy_accept_row_splits(T, V):
+    """Rows split into 64, 31, 22 and 16 ranges (the combining kernel gives a
+    row the next power of two of lanes, one or several passes over the rows),
+    ranges without a column included."""
+    ws = ss.workspace(ss.greedy_accept_workspace_bytes(T), dev())
+    lg, parent, tokens = _case(T, V, 1, 10 * T + V)
+    am, outs = _run(lg, parent, tokens, V, ws)
+    ref = oracle.greedy_accept(np.ascontiguousarray(lg[:, :V]), tokens, parent)
+    assert np.array_equal(am, ref[0]) and tuple(outs) == tuple(ref[1:])
+
+
 def test_greedy_accept_invalid_tree():
     T, V = 9, 300
     lg, parent, tokens = _case(T, V, 0, 5)

@@ -74,6 +74,24 @@ def test_topk_matches_oracle(n, V, k, pad):
     assert np.array_equal(tok, tok2) and np.array_equal(lp, lp2)
 
 
+@pytest.mark.parametrize("V", [4193799, 4193800, 4300007])
+def test_topk_ranges_up_to_and_past_16_bit_indices(V):
+    """One row over 64 ranges of 65528 columns (and 7 past the last whole
+    vector): the most that a 32-bit key's index holds; then wider ranges,
+    which take 64-bit keys.  The best logits lie at the last columns, and a
+    tie across two ranges goes to the lower index.  The sum has 33 times the
+    terms of the largest case above in the same pairwise tree, 6 levels
+    deeper, so the same absolute bound holds with room."""
+    lg = _logits(1, V, 0, seed=V)
+    f = lg.view(np.float16)
+    f[0, V - 3:V] = np.float16(11.0)
+    f[0, [70000, 65528 * 5 + 17]] = np.float16(10.5)
+    tok, lp, _ = _run(lg, V, 8)
+    otok, olp = oracle.topk_logprobs(lg[:, :V], 8)
+    assert np.array_equal(tok, otok)
+    assert np.abs(lp.astype(np.float64) - olp).max() <= LP_ATOL
+
+
 def test_topk_best_entries_in_one_range():
     """All k best logits of a row inside one workgroup's range (consecutive
     indices), so one partial list supplies every entry."""
