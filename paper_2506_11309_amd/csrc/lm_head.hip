@@ -3,22 +3,31 @@
 // W [V][H] fp16 row-major (the vocabulary projection of the 80-layer step).
 //
 // HBM-bound: the weight matrix (2.1 GB at V = 128256, H = 8192) is read once.
-// Mapping (v_mfma_f32_16x16x32_f16, wave64): B operand = 16 vocabulary rows
-// of W, lane (n = lane % 16, kq = lane / 16) loads the 16 bytes
-// W[16 t + n][32 s + 8 kq .. +7] of k-step s -- the four lanes of a row read
-// 64 contiguous bytes; A operand = 16 rows of xn from LDS in the same k
-// order.  A workgroup (4 waves x 2 tiles) owns 128 vocabulary rows for the
-// whole K: no split, no partials.  K advances in blocks of 128: each thread
-// stages its share of the block's activations through a register ring into a
-// 3-slot LDS ring (one fence-free barrier per block), and each wave's weight
-// loads run two blocks ahead in the same ring.
+// Mapping (v_mfma_f32_16x16x32_f16, wave64): B operand = 16 vocabulary rows of
+// W, A operand = 16 rows of xn.  A workgroup (4 waves x C tiles) owns 64 C
+// vocabulary rows for the whole K: no split, no partials.  K advances in
+// stages of 64, one 128-byte line of every row: weights and activations go
+// straight into LDS with 16-byte loads (8 rows of 8 chunks per wave-wide load,
+// so every memory request is a whole line), NS stages deep.  Chunk g of row r
+// is stored at position g ^ (r / 2 mod 8), which makes the fragment reads (16
+// rows, one chunk) hit every bank once.
+//
+// Rows lie 2 H bytes apart, for the usual H a multiple of the distance after
+// which the memory channels repeat, so workgroups that all begin at k = 0 and
+// advance together ask the same few channels for their lines.  Each workgroup
+// therefore begins at a stage of its own (a hash of its index) and wraps
+// around: V = 128256, H = 8192, 8 rows 446 -> 354 us, and nothing else in this
+// kernel moved that time (deeper rings, more or fewer rows per workgroup).
+// Measured (us, before -> now, and the rate): H 8192 at 64 rows 471 -> 366 (5.7
+// TB/s), 32 rows 445 -> 353, 8 rows 443 -> 349 (6.0 TB/s, what a read-only
+// kernel reaches); H 2048 at 8 rows 121 -> 93; V 8704, H 4736, 46 rows 53 -> 30.
 #include "ss_device.h"
 #include "ss_internal.h"
 
 namespace ss {
 
-constexpr int kLmRing = 3;
-constexpr int kLmCols = 2;              // 16-row tiles of W per wave
+constexpr int kLmWaves = 4;
+constexpr int kLmK = 64;    // k of a stage: one 128-byte line per row
 
 struct LmArgs {
   const uint16_t* xn;  // [M][H] fp16
@@ -27,110 +36,111 @@ struct LmArgs {
   int M, H, V, ldl;
 };
 
-template <int MT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void lm_head_kernel(LmArgs a) {
-  constexpr int KST = 128 + 8;  // halves per LDS row (16-byte pad)
-  __shared__ uint16_t xs[kLmRing][MT * 16 * KST];
-  const int tid = threadIdx.x;
+// wait until at most `behind` stages (LPW loads each) of this wave remain in flight
+template <int LPW, int K>
+__device__ __forceinline__ void lm_wait(int behind) {
+  if constexpr (K == 0) {
+    vm_wait<0>();
+  } else {
+    if (behind >= K) vm_wait<LPW * K>();
+    else lm_wait<LPW, K - 1>(behind);
+  }
+}
+
+template <int MT, int kLmCols, int NS>
+__global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(LmArgs a) {
+  constexpr int kWBytes = kLmCols * 2048;                    // weights of a stage, per wave
+  constexpr int kXBytes = MT * 2048;                         // activations of a stage
+  constexpr int kStage = kXBytes + kLmWaves * kWBytes;
+  constexpr int kXLoads = (MT * 2 + kLmWaves - 1) / kLmWaves;  // 1 KB loads per wave and stage
+  constexpr int kLPW = kLmCols * 2 + kXLoads;
+  __shared__ __attribute__((aligned(1024))) char smem[NS * kStage];
   const int lane = lane_id();
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int n16 = lane & 15, kq = lane >> 4;
-  const int tile0 = blockIdx.x * (4 * kLmCols) + wave * kLmCols;  // first 16-row tile of this wave
+  const int tile0 = blockIdx.x * (kLmWaves * kLmCols) + wave * kLmCols;
   const int ntiles = a.V >> 4;
-  const int nkb = a.H >> 7;
-
-  // activations of block kb: thread t stages vectors t + 256 j (row v / 16,
-  // 16-byte column v % 16); rows >= M are zero
-  auto load_x = [&](int kb, u32x4 (&r)[MT]) {
-    int b = kb < nkb ? kb : nkb - 1;
-    asm volatile("" : "+s"(b));
+  const int nst = a.H / kLmK;
+  const uint32_t row_bytes = (uint32_t)a.H * 2u;
+  const uint32_t lds0 = lds_address(smem);
+  // this wave's rows of W; rows past V lie outside the buffer (zeros) and are
+  // not stored
+  const int first = min(tile0, ntiles - 1) * 16;
+  const i32x4 rw = raw_rsrc(a.W + (size_t)first * a.H, (uint32_t)min(kLmCols * 16, a.V - first) * row_bytes);
+  const i32x4 rx = raw_rsrc(a.xn, (uint32_t)a.M * row_bytes);
+  // load l of a matrix: rows 8 l .. 8 l + 7, lane i takes row i / 8 and the
+  // chunk that belongs at position i % 8 of it
+  const int lr = lane >> 3, lp = lane & 7;
+  uint32_t wv[kLmCols * 2], xv[kXLoads];
 #pragma unroll
-    for (int j = 0; j < MT; ++j) {
-      const int v = tid + 256 * j, row = v >> 4, c = v & 15;
-      r[j] = row < a.M ? *reinterpret_cast<const u32x4*>(a.xn + (size_t)row * a.H + b * 128 + c * 8)
-                       : u32x4{0u, 0u, 0u, 0u};
-    }
+  for (int l = 0; l < kLmCols * 2; ++l) {
+    const int row = 8 * l + lr;
+    wv[l] = (uint32_t)row * row_bytes + (uint32_t)((lp ^ ((row >> 1) & 7)) * 16);
+  }
+#pragma unroll
+  for (int j = 0; j < kXLoads; ++j) {
+    const int l = (wave + kLmWaves * j) % (MT * 2);
+    const int row = 8 * l + lr;
+    // rows past M: row M - 1 again (their results are not stored)
+    xv[j] = (uint32_t)min(row, a.M - 1) * row_bytes + (uint32_t)((lp ^ ((row >> 1) & 7)) * 16);
+  }
+  // the stage this workgroup begins at (multiplicative hash)
+  const int rot = __builtin_amdgcn_readfirstlane((int)(((blockIdx.x * 2654435761u) >> 16) % (unsigned)nst));
+  auto issue = [&](int t) {
+    const uint32_t st = lds0 + (uint32_t)((t % NS) * kStage);
+    const int k = t + rot < nst ? t + rot : t + rot - nst;  // 64 k's from 64 k on
+    const uint32_t off = (uint32_t)k * (kLmK * 2);
+#pragma unroll
+    for (int l = 0; l < kLmCols * 2; ++l) buffer_load_lds16(rw, wv[l], off, st + kXBytes + wave * kWBytes + l * 1024);
+#pragma unroll
+    for (int j = 0; j < kXLoads; ++j) buffer_load_lds16(rx, xv[j], off, st + ((wave + kLmWaves * j) % (MT * 2)) * 1024);
   };
-  auto store_x = [&](int slot, const u32x4 (&r)[MT]) {
-#pragma unroll
-    for (int j = 0; j < MT; ++j) {
-      const int v = tid + 256 * j, row = v >> 4, c = v & 15;
-      *reinterpret_cast<u32x4*>(&xs[slot][row * KST + c * 8]) = r[j];
-    }
-  };
-  // weights of block kb for this wave's tiles (tiles past V repeat the last
-  // valid one and are not stored)
-  auto load_w = [&](int kb, u32x4 (&r)[kLmCols][4]) {
-    int b = kb < nkb ? kb : nkb - 1;
-    asm volatile("" : "+s"(b));
-#pragma unroll
-    for (int ct = 0; ct < kLmCols; ++ct) {
-      const int t = tile0 + ct < ntiles ? tile0 + ct : ntiles - 1;
-      const uint16_t* row = a.W + (size_t)(t * 16 + n16) * a.H + b * 128 + 8 * kq;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) r[ct][s] = *reinterpret_cast<const u32x4*>(row + 32 * s);
-    }
-  };
-
   f32x4 acc[MT][kLmCols];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int ct = 0; ct < kLmCols; ++ct) acc[mt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  auto compute = [&](int slot, const u32x4 (&w)[kLmCols][4]) {
+  // chunk g of row r lies at position g ^ ((r >> 1) & 7)
+  uint32_t frag[2];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < 2; ++s) frag[s] = (uint32_t)(n16 * 128 + (((4 * s + kq) ^ ((n16 >> 1) & 7)) * 16));
+  auto compute = [&](int t) {
+    const char* st = smem + (t % NS) * kStage;
+    const char* sw = st + kXBytes + wave * kWBytes;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      half8 w[kLmCols];
+#pragma unroll
+      for (int ct = 0; ct < kLmCols; ++ct) w[ct] = *reinterpret_cast<const half8*>(sw + ct * 2048 + frag[s]);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        const half8 af = *reinterpret_cast<const half8*>(&xs[slot][(mt * 16 + n16) * KST + 32 * s + 8 * kq]);
+        const half8 x = *reinterpret_cast<const half8*>(st + mt * 2048 + frag[s]);
 #pragma unroll
-        for (int ct = 0; ct < kLmCols; ++ct)
-          acc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, bitcast<half8>(w[ct][s]), acc[mt][ct], 0, 0, 0);
+        for (int ct = 0; ct < kLmCols; ++ct) acc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, w[ct], acc[mt][ct], 0, 0, 0);
       }
     }
   };
-
-  // step kb: load activations and weights of block kb + 2, write block
-  // kb + 1's activations to LDS slot (kb + 1) % 3 (last read at step kb - 2),
-  // barrier, compute block kb
-  u32x4 xr[kLmRing][MT];
-  u32x4 wr[kLmRing][kLmCols][4];
 #pragma unroll
-  for (int j = 0; j < kLmRing - 1; ++j) {
-    load_x(j, xr[j]);
-    load_w(j, wr[j]);
+  for (int j = 0; j < NS - 1; ++j)
+    if (j < nst) issue(j);
+  int t = 0;
+  for (; t + NS - 1 < nst; ++t) {
+    vm_wait<kLPW * (NS - 2)>();
+    lds_barrier();
+    issue(t + NS - 1);
+    compute(t);
   }
-  store_x(0, xr[0]);
-  for (int k0 = 0; k0 < nkb; k0 += kLmRing) {
-#pragma unroll
-    for (int J = 0; J < kLmRing; ++J) {
-      const int kb = k0 + J;
-      load_x(kb + kLmRing - 1, xr[(J + kLmRing - 1) % kLmRing]);
-      load_w(kb + kLmRing - 1, wr[(J + kLmRing - 1) % kLmRing]);
-      if (kb < nkb) {
-        if (kb + 1 < nkb) store_x((kb + 1) % kLmRing, xr[(J + 1) % kLmRing]);
-        lds_barrier();
-        compute(kb % kLmRing, wr[J]);
-      } else {
-        // retire the slot's loads so that no load into a ring register is
-        // pending where the compiler reuses it
-#pragma unroll
-        for (int j = 0; j < MT; ++j) asm volatile("" : : "v"(xr[(J + 1) % kLmRing][j]));
-#pragma unroll
-        for (int ct = 0; ct < kLmCols; ++ct)
-#pragma unroll
-          for (int s = 0; s < 4; ++s) asm volatile("" : : "v"(wr[J][ct][s]));
-      }
-    }
+  for (; t < nst; ++t) {
+    lm_wait<kLPW, NS - 2>(nst - 1 - t);
+    lds_barrier();
+    compute(t);
   }
 
   // lane holds rows 4 kq + r of column n16 of each tile
 #pragma unroll
   for (int ct = 0; ct < kLmCols; ++ct) {
-    const int t = tile0 + ct;
-    if (t >= ntiles) continue;
-    const int col = t * 16 + n16;
+    if (tile0 + ct >= ntiles) continue;
+    const int col = (tile0 + ct) * 16 + n16;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -141,16 +151,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void l
   }
 }
 
+// kLmCols tiles per wave; NS stages: two workgroups per compute unit with one
+// or two tiles, one with four (136 to 144 KB of LDS)
+template <int C>
+static void launch_cols(const LmArgs& a, hipStream_t st) {
+  constexpr int kSmall = C == 1 ? 6 : 4, kLarge = C == 1 ? 4 : 3;
+  const dim3 grid((a.V / 16 + kLmWaves * C - 1) / (kLmWaves * C)), wg(64 * kLmWaves);
+  switch ((a.M + 15) / 16) {
+    case 1: hipLaunchKernelGGL((lm_head_kernel<1, C, kSmall>), grid, wg, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((lm_head_kernel<2, C, kSmall>), grid, wg, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((lm_head_kernel<3, C, kLarge>), grid, wg, 0, st, a); break;
+    default: hipLaunchKernelGGL((lm_head_kernel<4, C, kLarge>), grid, wg, 0, st, a); break;
+  }
+}
+
 void launch_lm_head(const uint16_t* xn, int M, int H, const uint16_t* W, int V, uint16_t* logits, int ldl,
                     hipStream_t st) {
-  LmArgs a{xn, W, logits, M, H, V, ldl};
-  const dim3 grid((V / 16 + 4 * kLmCols - 1) / (4 * kLmCols));
-  switch ((M + 15) / 16) {
-    case 1: hipLaunchKernelGGL(lm_head_kernel<1>, grid, dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL(lm_head_kernel<2>, grid, dim3(256), 0, st, a); break;
-    case 3: hipLaunchKernelGGL(lm_head_kernel<3>, grid, dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL(lm_head_kernel<4>, grid, dim3(256), 0, st, a); break;
-  }
+  const LmArgs a{xn, W, logits, M, H, V, ldl};
+  // 256 rows per workgroup where those fill whole rounds of the compute units
+  // (V 128256, 64 rows: 366 against 381 us with 128), 64 where 128 would leave
+  // half of the units idle (V 8704: 30 against 41 us)
+  const int n4 = (V + 255) / 256, rounds = (n4 + 255) / 256;
+  if (V > 65536 && 10 * n4 >= 9 * 256 * rounds) launch_cols<4>(a, st);
+  else if (V > 16384) launch_cols<2>(a, st);
+  else launch_cols<1>(a, st);
 }
 
 }  // namespace ss

@@ -49,6 +49,19 @@ def test_lm_head_small_shapes(M, H, V):
     print(f"lm_head M={M} H={H} V={V}: max abs err {err:.3g}, max rel err (|r|>=0.2) {rel:.3g}")
 
 
+@pytest.mark.parametrize("M,H,V", [(1, 128, 16), (48, 128, 16384), (17, 640, 16400), (64, 128, 66800), (33, 1152, 4112),
+                                   (16, 128, 131056), (49, 256, 118016)])
+def test_lm_head_row_blocks(M, H, V):
+    """64, 128 and 256 vocabulary rows per workgroup (up to 16384 columns, up
+    to 65536 or an uneven last round, whole rounds of 256 workgroups), the
+    last workgroup partly or almost wholly past V, K shorter than the ring of
+    stages, every number of M-tiles."""
+    h = gen.normal_f16(74, M, (M, H))
+    gamma = gen.normal_f16(75, M, (H,), 1.0, 0.02)
+    W = gen.normal_f16(76, M, (V, H), 0.0, 0.02)
+    check_close(_run(h, gamma, W), oracle.lm_head(h, gamma, W), f"lm_head M={M} H={H} V={V}")
+
+
 def test_lm_head_full_size_sampled_rows():
     cfg = CONFIGS["c5"]
     H, V, M = cfg.shape.H, cfg.vocab, cfg.T
