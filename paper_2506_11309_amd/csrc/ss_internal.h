@@ -30,6 +30,7 @@ struct GemmLaunch {
   int nwg;      // workgroups launched
   int ksw;      // > 0: K-split workgroups of ksw waves (no partials), knt weight tiles each
   int knt;      // (counting gate and up tiles for SwiGLU)
+  bool wide;    // wide blocks: nwg / nblocks K ranges
   bool swiglu;
   float* part;  // split-K partial slots (2 per workgroup)
 };
@@ -40,6 +41,7 @@ constexpr int kNormGroupsPerWave = 2;
 
 struct GemmPlan {
   int nw, nblocks, nwg, ksw = 0, knt = 0;
+  bool wide = false;
   size_t part_bytes;  // split partials
   size_t prep_bytes;  // prepared activations of the input
 };

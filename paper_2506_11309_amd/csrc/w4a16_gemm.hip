@@ -20,12 +20,16 @@
 //     sum of a group is C_g = sum_k x (q - z), and the accumulator takes
 //     s C_g (one mixed-precision FMA per output element, fp16 s read in
 //     place).
-//   * Stream-K scheduling: a fixed grid of workgroups (4 waves each) splits
-//     the (N-block, group) iteration space into equal contiguous ranges; the
-//     4 waves split an N-block's columns.  Per group, every wave loads 1 KB
-//     contiguous blocks of its own weight tiles and a quarter of the group's
-//     activation fragments into a register ring (6 groups deep up to 32
-//     rows, 4 above), issued together so that the in-order vmcnt queue never
+// Three forms share that mapping; plan_w4a16_gemm picks one by M, K and N:
+//   * K-split workgroups (few rows, or a matrix small enough that reading
+//     the activations once per few columns costs little);
+//   * wide blocks (17 rows and more over a large matrix);
+//   * stream-K, for the shapes between: a fixed grid of workgroups (4 waves
+//     each) splits the (N-block, group) iteration space into equal
+//     contiguous ranges; the 4 waves split an N-block's columns.  Per group,
+//     every wave loads 1 KB contiguous blocks of its own weight tiles and a
+//     quarter of the group's activation fragments into a register ring (3
+//     groups deep), issued together so that the in-order vmcnt queue never
 //     holds a weight prefetch behind an older activation load; the
 //     activations pass through a 3-slot LDS ring shared by the 4 waves, with
 //     one fence-free barrier per group.  An N-block split between
@@ -512,6 +516,301 @@ __global__ __launch_bounds__(256) void w4a16_fixup_kernel(GemmArgs a) {
   ep.write(a, nb, wave, lane, acc, mt0 * 16);
 }
 
+// ------------------------------------------------------------ wide blocks
+// Many rows over a large matrix.  One workgroup of 8 waves owns 16
+// weight tiles (plain: 256 columns; a fused SwiGLU: the gate and up tiles of
+// 128) over one of S equal K ranges, two tiles per wave, and a step is one
+// 128-k group.  The activation fragments of a group are read from L2 once
+// per 16 weight tiles (4 or 8 in the stream-K kernel) and shared through a
+// 3-slot LDS ring.  What bounds it is instruction issue: per group a SIMD's
+// two waves have 8 MT MFMAs each and the dequantisation of two blocks, and
+// with one workgroup per compute unit nothing hides a wave that does one
+// after the other.  So a step interleaves them: the products of each M-tile
+// stand beside the LDS reads of the next M-tile's fragments, the previous
+// M-tile's group sums times their scales, and a share of the next group's
+// dequantisation; no instruction waits for the MFMA just issued.  Loads are
+// four (weights) and five (activations) groups ahead in registers.
+// Every element sums its groups in the order of the stream-K kernel.
+// With S > 1 the ranges' partial sums go to memory and the fix-up kernel
+// adds them in range order (deterministic).
+// Measured against the stream-K kernel (us, weights rotated through HBM; 32
+// / 45 / 64 rows): SwiGLU K 8192, N 28672 59.0 -> 58.3, 74.6 -> 69.1, 94.2
+// -> 83.8 (3.0 TB/s of weights at 64 rows); K 28672, N 8192 39.0 -> 36.2,
+// 44.4 -> 42.0, 53.6 -> 48.0.
+constexpr int kWideW = 8;     // waves of a workgroup
+constexpr int kWideStep = 4;  // K ranges are multiples of this many groups (the register ring's length)
+
+template <int MT, bool SW>
+__global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))) void w4a16_wide_kernel(GemmArgs a) {
+  constexpr int W = kWideW, NT = 2, kC = SW ? 1 : 2;  // weight and output column tiles per wave
+  constexpr int kF = MT * 4;                          // activation fragments of a group
+  constexpr int kLA = (kF + W - 1) / W;               // staged per wave
+  constexpr int kR = kWideStep, kL = 3;
+  __shared__ u32x4 abuf[kL][kF][kWave];
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int ncol = lane & 15, kq = lane >> 4;
+  const int G = a.G, ntiles = a.N >> 4, S = a.nwg / a.nblocks, NS = G / kR;
+  const int b = blockIdx.x;
+  const int v = (a.nwg % 8 == 0) ? (b % 8) * (a.nwg / 8) + b / 8 : b;
+  const int nb = __builtin_amdgcn_readfirstlane(v / S), sp = v - nb * S;  // block and K range
+  const int s_lo = __builtin_amdgcn_readfirstlane(sp * NS / S);
+  const int g_lo = s_lo * kR, total = (__builtin_amdgcn_readfirstlane((sp + 1) * NS / S) - s_lo) * kR;
+  const uint32_t q_bytes = (uint32_t)((size_t)a.K * a.N / 2), sz_bytes = (uint32_t)((size_t)a.N * G * 4);
+  const auto rq0 = buffer_rsrc(a.w0.q, q_bytes), rs0 = buffer_rsrc(a.w0.sz, sz_bytes);
+  const auto rq1 = buffer_rsrc(SW ? a.w1.q : a.w0.q, q_bytes), rs1 = buffer_rsrc(SW ? a.w1.sz : a.w0.sz, sz_bytes);
+  const auto ra = buffer_rsrc(a.a, (uint32_t)(MT * G * 4 * kWave * 16));
+  const uint32_t lane16 = (uint32_t)lane * 16u, col4 = (uint32_t)ncol * 4u;
+  const int t0 = nb * (W * kC) + wave * kC;  // first output column tile of the wave
+  // tiles past the matrix (N / 16 not a multiple of a block's) repeat the last one and are not written
+  auto clampt = [&](int t) { return t < ntiles ? t : ntiles - 1; };
+  const uint32_t tq0 = (uint32_t)(clampt(t0) * G), tq1 = SW ? tq0 : (uint32_t)(clampt(t0 + 1) * G);
+
+  struct Raw {
+    u32x4 b[NT];
+    uint32_t sz[NT];
+  };
+  Raw raw[kR];
+  u32x4 ar[kR][kLA];
+  auto load_a = [&](u32x4 (&r)[kLA], int i) {
+    const int g = g_lo + (i < total ? i : total - 1);
+#pragma unroll
+    for (int j = 0; j < kLA; ++j) {
+      int f = wave + W * j;
+      f = f < kF ? f : wave % kF;
+      r[j] = buffer_load_x4(ra, lane16, (uint32_t)((((f >> 2) * G + g) * 4 + (f & 3)) * 1024));
+    }
+  };
+  auto load_b = [&](Raw& r, int i) {
+    const int g = g_lo + (i < total ? i : total - 1);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const uint32_t tg = (nt ? tq1 : tq0) + (uint32_t)g;
+      r.b[nt] = buffer_load_x4(SW && nt ? rq1 : rq0, lane16, tg * 1024u);
+      r.sz[nt] = buffer_load_x1(SW && nt ? rs1 : rs0, col4, tg * 64u);
+    }
+  };
+  auto store_a = [&](int slot, const u32x4 (&r)[kLA]) {
+#pragma unroll
+    for (int j = 0; j < kLA; ++j) {
+      int f = wave + W * j;
+      f = f < kF ? f : wave % kF;
+      abuf[slot][f][lane] = r[j];
+    }
+  };
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  uint32_t magic_lo = 0x64006400u, magic_hi = 0x54005400u;
+  asm volatile("" : "+v"(magic_lo), "+v"(magic_hi));
+  {
+    // prologue: groups 0 .. 3 in flight; groups 0 and 1 staged
+#pragma unroll
+    for (int j = 0; j < kR; ++j) {
+      load_a(ar[j], j);
+      load_b(raw[j], j);
+    }
+    BFrag bf[2][NT];
+    float sc[2][NT];
+    half8 af[2][4];
+    f32x4 cs[2][NT];
+    float sprev[NT];  // the previous group's scales
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      cs[0][nt] = cs[1][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      sprev[nt] = 0.f;
+    }
+    store_a(0, ar[0]);
+    store_a(1, ar[1]);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      bf[0][nt] = dequant_block(raw[0].b[nt], raw[0].sz[nt], magic_lo, magic_hi);
+      sc[0][nt] = (float)bitcast<half2v>(raw[0].sz[nt])[0];
+    }
+    load_a(ar[0], 4);
+    load_a(ar[1], 5);
+    load_b(raw[0], 4);
+    lds_barrier();
+#pragma unroll
+    for (int f = 0; f < 4; ++f) af[0][f] = bitcast<half8>(abuf[0][f][lane]);
+    int sl = 0;  // LDS slot of group i
+    for (int i0 = 0; i0 < total; i0 += kR) {
+#pragma unroll
+      for (int J = 0; J < kR; ++J) {
+        const int i = i0 + J;
+        const int P = J & 1;
+        const int sl1 = sl == 2 ? 0 : sl + 1, sl2 = sl1 == 2 ? 0 : sl1 + 1;
+        // group i + 2 to LDS (slot read last at step i - 1), its registers refilled with group i + 6
+        store_a(sl2, ar[(J + 2) % kR]);
+        load_a(ar[(J + 2) % kR], i + 6);
+        const Raw& rn = raw[(J + 1) % kR];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const int pm = (J * MT + mt) & 1;
+          // fragments of the next M-tile (of the next group after the last)
+#pragma unroll
+          for (int f = 0; f < 4; ++f)
+            af[pm ^ 1][f] = bitcast<half8>(mt + 1 < MT ? abuf[sl][(mt + 1) * 4 + f][lane] : abuf[sl1][f][lane]);
+#pragma unroll
+          for (int f = 0; f < 4; ++f)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              const half8 bb = f == 0 ? bf[P][nt].lo_a : f == 1 ? bf[P][nt].lo_b : f == 2 ? bf[P][nt].hi_a : bf[P][nt].hi_b;
+              const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+              cs[pm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[pm][f], bb, f == 0 ? z : cs[pm][nt], 0, 0, 0);
+            }
+          // previous M-tile's sums
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const float s = mt ? sc[P][nt] : sprev[nt];
+              acc[mt ? mt - 1 : MT - 1][nt][q] = __builtin_fmaf(cs[pm ^ 1][nt][q], s, acc[mt ? mt - 1 : MT - 1][nt][q]);
+            }
+          // a share of the next group's dequantisation: half h of tile nt
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              if ((nt * 2 + h) * MT / (2 * NT) == mt) {
+                const BFrag d = dequant_block(rn.b[nt], rn.sz[nt], magic_lo, magic_hi);
+                if (h == 0) {
+                  bf[P ^ 1][nt].lo_a = d.lo_a;
+                  bf[P ^ 1][nt].lo_b = d.lo_b;
+                } else {
+                  bf[P ^ 1][nt].hi_a = d.hi_a;
+                  bf[P ^ 1][nt].hi_b = d.hi_b;
+                  sc[P ^ 1][nt] = (float)bitcast<half2v>(rn.sz[nt])[0];
+                  asm("" : "+v"(sc[P ^ 1][nt]));
+                }
+              }
+          if (mt == MT - 1) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) sprev[nt] = sc[P][nt];
+          }
+        }
+        load_b(raw[(J + 1) % kR], i + 5);
+        lds_barrier();
+        sl = sl1;
+      }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[MT - 1][nt][q] = __builtin_fmaf(cs[(kR * MT - 1) & 1][nt][q], sprev[nt], acc[MT - 1][nt][q]);
+    // retire the loads past the end
+#pragma unroll
+    for (int j = 0; j < kR; ++j) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) asm volatile("" : : "v"(raw[j].b[nt]), "v"(raw[j].sz[nt]));
+#pragma unroll
+      for (int f = 0; f < kLA; ++f) asm volatile("" : : "v"(ar[j][f]));
+    }
+  }
+  if (S == 1) {
+    const int G2 = a.N >> 7;
+#pragma unroll
+    for (int c = 0; c < kC; ++c) {
+      const int t = t0 + c;
+      if (t < ntiles) {
+        const int col = t * 16 + ncol;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int m = mt * 16 + 4 * kq + r;
+            if (m < a.M) {
+              float val;
+              if constexpr (SW) {
+                const float gte = acc[mt][0][r];
+                val = gte / (1.0f + __expf(-gte)) * acc[mt][1][r];
+              } else {
+                val = acc[mt][c][r] + (a.res ? h2f(a.res[(size_t)m * a.ldr + col]) : 0.f);
+              }
+              const uint16_t h = f2h(val);
+              if (a.y) a.y[(size_t)m * a.ldy + col] = h;
+              if (a.yp) store_prepared(a.yp, m, col, G2, h);
+            }
+          }
+      }
+    }
+  } else {
+    float* mine = a.part + (((size_t)v * W + wave) * MT * NT * kWave + lane) * 4;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        *reinterpret_cast<f32x4*>(mine + (size_t)(mt * NT + nt) * kWave * 4) = acc[mt][nt];
+  }
+}
+
+// The K ranges' partial sums of wide blocks, one wave per (block, M-tile,
+// wave of the block), eight ranges' loads in flight.
+template <int MT, bool SW>
+__global__ __launch_bounds__(256) void w4a16_wide_fixup_kernel(GemmArgs a) {
+  constexpr int WB = kWideW, kBatch = 8, NT = 2, kC = SW ? 1 : 2;
+  const int S = a.nwg / a.nblocks;
+  const int x = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wave = x % WB, mt = (x / WB) % MT, nb = x / (WB * MT);
+  const int lane = lane_id();
+  const int ncol = lane & 15, kq = lane >> 4, ntiles = a.N >> 4;
+  const int t0 = nb * WB * kC + wave * kC;
+  float rv[kC][4];
+#pragma unroll
+  for (int c = 0; c < kC; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = mt * 16 + 4 * kq + r, t = t0 + c;
+      rv[c][r] = (!SW && a.res && m < a.M && t < ntiles) ? h2f(a.res[(size_t)m * a.ldr + t * 16 + ncol]) : 0.f;
+    }
+  f32x4 acc[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < S; c0 += kBatch) {
+    f32x4 pa[kBatch][NT];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int c = min(c0 + j, S - 1);
+      const float* src = a.part + ((((size_t)(nb * S + c) * WB + wave) * MT + mt) * NT * kWave + lane) * 4;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) pa[j][nt] = *reinterpret_cast<const f32x4*>(src + nt * kWave * 4);
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      if (c0 + j >= S) break;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] += pa[j][nt];
+    }
+  }
+  const int G2 = a.N >> 7;
+#pragma unroll
+  for (int c = 0; c < kC; ++c) {
+    const int t = t0 + c;
+    if (t < ntiles) {
+      const int col = t * 16 + ncol;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = mt * 16 + 4 * kq + r;
+        if (m < a.M) {
+          float val;
+          if constexpr (SW) {
+            const float gte = acc[0][r];
+            val = gte / (1.0f + __expf(-gte)) * acc[1][r];
+          } else {
+            val = acc[c][r] + rv[c][r];
+          }
+          const uint16_t h = f2h(val);
+          if (a.y) a.y[(size_t)m * a.ldy + col] = h;
+          if (a.yp) store_prepared(a.yp, m, col, G2, h);
+        }
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------- K-split workgroups
 // One workgroup owns kC 16-column output tiles (a fused SwiGLU: their gate
 // and up tiles) over the whole K range; its W waves take contiguous group
@@ -876,9 +1175,8 @@ void launch_prepack_w4(const uint8_t* q, const uint16_t* s, const uint8_t* z, in
 
 // ----------------------------------------------------------------- launch
 
-template <int MT, int NW, int EPI>
-static void launch_t(const GemmLaunch& L, hipStream_t st) {
-  GemmArgs a;
+static GemmArgs gemm_args(const GemmLaunch& L) {
+  GemmArgs a = {};
   auto unpack = [&](const void* p) {
     return W4Ptr{reinterpret_cast<const u32x4*>(p),
                  reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(p) + (size_t)L.K * L.N / 2)};
@@ -899,6 +1197,16 @@ static void launch_t(const GemmLaunch& L, hipStream_t st) {
   a.nwg = L.nwg;
   a.units = (uint32_t)(L.nblocks * a.G);
   a.part = L.part;
+  a.x = L.xnorm;
+  a.ldx = L.ldx;
+  a.gamma = L.gamma;
+  a.eps = L.eps;
+  return a;
+}
+
+template <int MT, int NW, int EPI>
+static void launch_t(const GemmLaunch& L, hipStream_t st) {
+  const GemmArgs a = gemm_args(L);
   hipLaunchKernelGGL((w4a16_gemm_kernel<MT, NW, EPI>), dim3(L.nwg), dim3(256), 0, st, a);
   // ranges split no N-block when every workgroup gets whole N-blocks
   if (L.nblocks % L.nwg != 0)
@@ -927,35 +1235,26 @@ static void launch_mt(const GemmLaunch& L, hipStream_t st) {
   }
 }
 
-static GemmArgs kslice_args(const GemmLaunch& L) {
-  GemmArgs a = {};
-  auto unpack = [&](const void* p) {
-    return W4Ptr{reinterpret_cast<const u32x4*>(p),
-                 reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(p) + (size_t)L.K * L.N / 2)};
-  };
-  a.w0 = unpack(L.w0);
-  a.w1 = unpack(L.w1);
-  a.K = L.K;
-  a.N = L.N;
-  a.G = L.K / 128;
-  a.a = L.aprep;
-  a.M = L.M;
-  a.y = L.y;
-  a.ldy = L.ldy;
-  a.yp = L.yprep;
-  a.res = L.res;
-  a.ldr = L.ldr;
-  a.x = L.xnorm;
-  a.ldx = L.ldx;
-  a.gamma = L.gamma;
-  a.eps = L.eps;
-  return a;
+template <int MT, bool SW>
+static void launch_wide(const GemmLaunch& L, hipStream_t st) {
+  const GemmArgs a = gemm_args(L);
+  hipLaunchKernelGGL((w4a16_wide_kernel<MT, SW>), dim3(L.nwg), dim3(64 * kWideW), 0, st, a);
+  if (L.nwg > L.nblocks)
+    hipLaunchKernelGGL((w4a16_wide_fixup_kernel<MT, SW>), dim3(L.nblocks * MT * kWideW / 4), dim3(256), 0, st, a);
+}
+template <bool SW>
+static void launch_wide_mt(const GemmLaunch& L, hipStream_t st) {
+  switch ((L.M + 15) / 16) {
+    case 2: launch_wide<2, SW>(L, st); break;
+    case 3: launch_wide<3, SW>(L, st); break;
+    default: launch_wide<4, SW>(L, st); break;
+  }
 }
 
 template <int W, int MT, int NT, bool SW>
 static void launch_ks(const GemmLaunch& L, hipStream_t st) {
   hipLaunchKernelGGL((w4a16_ksplit_kernel<W, MT, NT, SW>), dim3(L.N / 16 / (SW ? NT / 2 : NT)), dim3(64 * W), 0, st,
-                     kslice_args(L));
+                     gemm_args(L));
 }
 // MTX: the most M-tiles that the plan gives this form
 template <int W, int NT, bool SW, int MTX>
@@ -973,10 +1272,14 @@ static void launch_ks_mt(const GemmLaunch& L, hipStream_t st) {
 template <int W, int NT, bool SW>
 static void launch_ksn(const GemmLaunch& L, hipStream_t st) {
   hipLaunchKernelGGL((w4a16_ksplit_norm_kernel<W, NT, SW>), dim3(L.N / 16 / (SW ? NT / 2 : NT)), dim3(64 * W), 0, st,
-                     kslice_args(L));
+                     gemm_args(L));
 }
 
 void launch_w4a16_gemm(const GemmLaunch& L, hipStream_t st) {
+  if (L.wide) {
+    L.swiglu ? launch_wide_mt<true>(L, st) : launch_wide_mt<false>(L, st);
+    return;
+  }
   if (L.ksw && L.xnorm) {
     if (L.swiglu) {
       if (L.ksw == 8) L.knt == 2 ? launch_ksn<8, 2, true>(L, st) : launch_ksn<8, 4, true>(L, st);
@@ -1055,6 +1358,46 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
   p.ksw = MT == 1 && G >= 32 && p.knt <= 2 ? 16 : 8;
 }
 
+// Wide blocks (p.wide): where the matrix is large enough that a workgroup per
+// compute unit and K range has a long run of groups.  Lines from sweeps over 18
+// SwiGLU and 26 plain shapes (K 1536 .. 28672, N 2112 .. 32384) at 29, 45 and
+// 64 rows against the other two forms; S is the number of K ranges that
+// fills one round of the 256 compute units (two rounds were slower at every
+// shape: K 8192, N 26752, 64 rows 76 us at S = 1, 85 at 2), and shapes whose
+// round would stay under 200 workgroups (144 with S = 1, which needs no
+// partials) keep the other forms.
+static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
+  if (MT < 2 || K % (128 * kWideStep)) return;
+  const int nb = (tiles + (swiglu ? 8 : 16) - 1) / (swiglu ? 8 : 16);
+  const int ranges = K / (128 * kWideStep), fill = 256 / nb;
+  const int S = fill < ranges ? fill : ranges;
+  if (S < 1 || nb * S < (S == 1 ? 144 : 200)) return;
+  const double kn = 16.0 * tiles * K;
+  if (swiglu) {
+    // more column tiles than the K-split form takes: any K (K 1536, N 19776,
+    // 45 rows 16.6 -> 16.1 us; K 4608, N 19136, 64 rows 45.2 -> 39.3); below
+    // that, above 32 rows, a K long enough for two or three ranges (K 6144, N
+    // 16256, 64 rows 44.2 -> 38.7; K 4608, N 13568 32.7 -> 31.1; K 3584, N
+    // 14208 27.8 -> 28.3; up to 32 rows the K-split form, which asks for no
+    // partials, keeps its workspaces)
+    if (tiles <= 1088 && (tiles <= 512 || MT < 3 || K < 4608)) return;
+  } else {
+    // K 8192, N 21184, 29 rows 33.2 -> 30.0 us, 64 rows 45.5 -> 39.5; K
+    // 20480, N 5952 27.7 -> 25.9 and 35.0 -> 33.1; not K 9728, N 12096 (24.3
+    // -> 24.3 and 33.6 -> 31.5), K 8192, N 10240 (64 rows 27.7 -> 27.4, 32
+    // rows 19.3 -> 21.7) or K 14336, N 4096 (25.3 -> 26.2)
+    if (K < 8192 || tiles <= 256 || kn < (K >= 16384 ? 1.0e8 : 1.4e8)) return;
+  }
+  p.wide = true;
+  p.ksw = 0;
+  p.nblocks = nb;
+  p.nwg = nb * S;
+  // at least what the plan it replaces asks for, so that a workspace sized
+  // for some number of rows still serves every smaller one
+  const size_t part = S > 1 ? (size_t)p.nwg * kWideW * MT * 2 * kWave * 16 : 0;
+  if (part > p.part_bytes) p.part_bytes = part;
+}
+
 // The RMSNorm runs inside a K-split GEMM where no wave then holds more than
 // two groups (up to 2048 wide, one M-tile): every workgroup normalises all
 // of K for itself, so it pays while that is short (K 2048, N 3072, 8 rows:
@@ -1104,6 +1447,7 @@ GemmPlan plan_w4a16_gemm(int M, int K, int N, bool swiglu) {
   // a K-split plan writes no partials
   p.part_bytes = p.ksw ? 0 : (size_t)p.nwg * 2 * 4 * MT * col_w * src * kWave * 16;
   p.prep_bytes = (size_t)MT * (K / 128) * 4 * kWave * 16;
+  plan_wide(MT, K, tiles, swiglu, p);
   return p;
 }
 

@@ -189,6 +189,27 @@ def _gemm_case(M, K, N, seed, residual):
     return check_close(down16(dy), ref, f"gemm M={M} K={K} N={N}")
 
 
+def _gemm_sampled_case(M, K, N, seed, residual):
+    """Two calls agree bit for bit; sampled columns (the first and last 64,
+    256 random ones) against the oracle."""
+    W = _rand_w4(seed, N, K)
+    x = gen.normal_f16(seed, 1, (M, K))
+    r = gen.normal_f16(seed, 2, (M, N)) if residual else None
+    t, d = upload_w4(W)
+    outs = []
+    for _ in range(2):
+        dy = torch.zeros((M, N), dtype=torch.int16, device=dev())
+        ws = ss.workspace(ss.gemm_workspace_bytes(M, K, N), dev())
+        ss.w4a16_gemm(d, up(x), dy, ws, residual=up(r) if residual else None)
+        torch.cuda.synchronize()
+        outs.append(down16(dy))
+    assert np.array_equal(outs[0], outs[1])
+    cols = np.concatenate([np.arange(64), np.arange(N - 64, N),
+                           np.random.default_rng(35).choice(np.arange(64, N - 64), 256, replace=False)])
+    ref = oracle.w4a16_gemm(_w4_rows(W, cols), x, residual=r[:, cols] if residual else None)
+    check_close(outs[0][:, cols], ref, f"gemm M={M} K={K} N={N}")
+
+
 @pytest.mark.parametrize("M", [1, 8, 13, 16, 32, 40, 64])
 def test_w4a16_gemm_small_shapes_ragged_M(M):
     _gemm_case(M, 1024, 320, seed=M, residual=(M % 2 == 0))
@@ -368,6 +389,21 @@ def test_w4a16_k_split_forms(M, K, N, swiglu):
         _swiglu_sampled_case(M, K, N, seed=51 + M)
     else:
         _gemm_case(M, K, N, seed=M * 5 + K, residual=(M % 2 == 0))
+
+
+@pytest.mark.parametrize("M,K,N,swiglu", [
+    # one K range: of one step; the fewest and the most blocks, one cut off by the last column; 2 to 4 M-tiles
+    (17, 512, 18432, True), (64, 1536, 18496, True), (33, 1024, 32768, True),
+    # two and three (ranges of unequal length), above 32 rows only
+    (48, 4608, 13568, True), (64, 7168, 10112, True),
+    # plain: 2, 3 and 9 ranges, a block cut off by the last column
+    (32, 8192, 32768, False), (45, 8192, 21184, False), (64, 16896, 6208, False)])
+def test_w4a16_wide_blocks(M, K, N, swiglu):
+    """The wide blocks at the edges of their plan, against the oracle."""
+    if swiglu:
+        _swiglu_sampled_case(M, K, N, seed=61 + M)
+    else:
+        _gemm_sampled_case(M, K, N, seed=M * 7 + K, residual=(M % 2 == 0))
 
 
 @pytest.mark.parametrize("M,K,N,ldx,swiglu", [
