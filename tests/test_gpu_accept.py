@@ -86,6 +86,43 @@ def test_greedy_accept_row_splits(T, V):
     assert np.array_equal(am, ref[0]) and tuple(outs) == tuple(ref[1:])
 
 
+@pytest.mark.parametrize("T,V", [(3, 8), (64, 4101), (5, 100003)])
+def test_greedy_accept_special_values(T, V):
+    """Each row's choice is its largest number's first index: with quiet and
+    signalling NaNs (never chosen, and 0 for a row of nothing else),
+    infinities, equal values inside a vector and across vectors, zeros of
+    both signs, rows of -inf."""
+    lg, parent, tokens = _case(T, V, 0, 77 + T)
+    rng = np.random.default_rng(T)
+    lg = np.round(lg.view(np.float16) * 2)
+    bits = lg.view(np.uint16)
+    for r in range(T):
+        kind = r % 8
+        some = np.flatnonzero(rng.random(V) < 0.5)
+        if kind in (0, 1):
+            bits[r, some] = 0x7E01 if kind else 0x7C01
+            bits[r, rng.integers(0, V, V // 8)] = 0xFD02
+        elif kind == 2:
+            lg[r, :V] = -np.inf
+        elif kind == 3:
+            lg[r, :V] = -np.inf
+            bits[r, : V // 2] = 0x7D00
+        elif kind == 4:
+            lg[r, :V] = 0.0
+            lg[r, some] = -0.0
+        elif kind == 5:
+            bits[r, :V] = 0xFC01
+        elif kind == 6:
+            lg[r, some] = np.inf
+    ws = ss.workspace(ss.greedy_accept_workspace_bytes(T), dev())
+    am, _ = _run(bits, parent, tokens, V, ws)
+    ref = []
+    for x in lg[:, :V].astype(np.float32):
+        num = x[~np.isnan(x)]
+        ref.append(int(np.flatnonzero(x == num.max())[0]) if num.size else 0)
+    assert np.array_equal(am, np.array(ref))
+
+
 def test_greedy_accept_invalid_tree():
     T, V = 9, 300
     lg, parent, tokens = _case(T, V, 0, 5)
