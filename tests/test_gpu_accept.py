@@ -4,7 +4,7 @@ oracle, bit-exact (integer outputs from the same fp16 logits):
 * synthetic logits with planted ties, padded leading dimensions, random
   trees and draft tokens planted to match, over tree sizes 1..64 and
   vocabularies from 7 to 128256 entries (two calls in a row share one
-  workspace, so the ticket counter must come back to zero);
+  workspace);
 * an invalid tree: the error bit, choices still written, nothing else;
 * the closing step at the 80-layer configuration's shape (two layers, LM
   head over 128256 rows): verify, accept and commit on one stream, eagerly

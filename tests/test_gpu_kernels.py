@@ -406,6 +406,20 @@ def test_w4a16_wide_blocks(M, K, N, swiglu):
         _gemm_sampled_case(M, K, N, seed=M * 7 + K, residual=(M % 2 == 0))
 
 
+@pytest.mark.parametrize("M,K,N,swiglu", [
+    # plain, one and two tiles per wave, 1 to 4 M-tiles, split blocks
+    (8, 8320, 17472, False), (8, 8320, 17408, False), (17, 12800, 2048, False), (17, 16512, 2048, False),
+    (40, 8320, 2048, False), (40, 16512, 2048, False), (64, 8320, 2048, False), (64, 16512, 2048, False),
+    # SwiGLU: a K that is no multiple of the wide blocks' step
+    (8, 1152, 17472, True), (32, 1152, 17472, True), (47, 1152, 17472, True), (64, 1152, 17472, True)])
+def test_w4a16_stream_k_forms(M, K, N, swiglu):
+    """The stream-K form at the shapes that neither other form takes."""
+    if swiglu:
+        _swiglu_sampled_case(M, K, N, seed=71 + M)
+    else:
+        _gemm_sampled_case(M, K, N, seed=M * 3 + K, residual=(M % 2 == 0))
+
+
 @pytest.mark.parametrize("M,K,N,ldx,swiglu", [
     # norm inside the K-split GEMM: 2 groups per wave, then up to 4
     (8, 2048, 3072, 2048, False), (1, 2048, 3072, 2048, False), (6, 1024, 2048, 1032, False),
