@@ -535,8 +535,8 @@ __global__ __launch_bounds__(256) void w4a16_fixup_kernel(GemmArgs a) {
 // adds them in range order (deterministic).
 // Measured against the stream-K kernel (us, weights rotated through HBM; 32
 // / 45 / 64 rows): SwiGLU K 8192, N 28672 59.0 -> 58.3, 74.6 -> 69.1, 94.2
-// -> 83.8 (3.0 TB/s of weights at 64 rows); K 28672, N 8192 39.0 -> 36.2,
-// 44.4 -> 42.0, 53.6 -> 48.0.
+// -> 83.8 (3.0 TB/s of weights at 64 rows); K 28672, N 8192 at 45 and 64
+// rows 44.4 -> 42.0, 53.6 -> 48.0.
 constexpr int kWideW = 8;     // waves of a workgroup
 constexpr int kWideStep = 4;  // K ranges are multiples of this many groups (the register ring's length)
 
@@ -1381,11 +1381,17 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
     // 14208 27.8 -> 28.3; up to 32 rows the K-split form, which asks for no
     // partials, keeps its workspaces)
     if (tiles <= 1088 && (tiles <= 512 || MT < 3 || K < 4608)) return;
+    // up to 32 rows only a long K (weights read again from the Infinity
+    // Cache: K 3072, N 21120, 29 rows 21.8 -> 23.8 us; K 4608, N 19136, 20
+    // rows 31.6 -> 32.7; K 8192, N 22528, 29 rows 56.7 -> 54.4)
+    if (MT == 2 && K < 8192) return;
   } else {
-    // K 8192, N 21184, 29 rows 33.2 -> 30.0 us, 64 rows 45.5 -> 39.5; K
-    // 20480, N 5952 27.7 -> 25.9 and 35.0 -> 33.1; not K 9728, N 12096 (24.3
-    // -> 24.3 and 33.6 -> 31.5), K 8192, N 10240 (64 rows 27.7 -> 27.4, 32
-    // rows 19.3 -> 21.7) or K 14336, N 4096 (25.3 -> 26.2)
+    // above 32 rows K 8192, N 21184 39.7 -> 36.7 us (45 rows); K 20480, N
+    // 5952 36.3 -> 34.8 (64); K 28672, N 8192 54.8 -> 51.0 (64); not K 8192, N
+    // 10240 (27.7 -> 27.4) or K 14336, N 4096 (25.3 -> 26.2).  Up to 32 rows
+    // only many columns: K 12288, N 18432 40.1 -> 38.4, K 8192, N 21184 32.4
+    // -> 31.4; K 28672, N 8192 40.8 -> 41.1, K 20480, N 5952 25.1 -> 27.0
+    if (MT == 2 && tiles <= 1024) return;
     if (K < 8192 || tiles <= 256 || kn < (K >= 16384 ? 1.0e8 : 1.4e8)) return;
   }
   p.wide = true;

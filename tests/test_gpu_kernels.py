@@ -393,7 +393,7 @@ def test_w4a16_k_split_forms(M, K, N, swiglu):
 
 @pytest.mark.parametrize("M,K,N,swiglu", [
     # one K range: of one step; the fewest and the most blocks, one cut off by the last column; 2 to 4 M-tiles
-    (17, 512, 18432, True), (64, 1536, 18496, True), (33, 1024, 32768, True),
+    (17, 8192, 18432, True), (48, 512, 18432, True), (64, 1536, 18496, True), (33, 1024, 32768, True),
     # two and three (ranges of unequal length), above 32 rows only
     (48, 4608, 13568, True), (64, 7168, 10112, True),
     # plain: 2, 3 and 9 ranges, a block cut off by the last column
