@@ -1323,8 +1323,9 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
     if (tiles > 512 && MT >= 3 && (K > 4096 || tiles > 1024)) return;
     // gate + up of one column tile up to one workgroup per compute unit, and
     // where the activations are short or few (N 8640, K 3072, 4 rows: 10.2
-    // against 11.7 us; 29 rows 14.6 against 14.9)
-    p.knt = tiles <= 256 || (MT == 1 && K <= 2560) || (M <= 8 && tiles > 512) ? 2 : 4;
+    // against 11.7 us; 29 rows 14.6 against 14.9; N 7808, K 4608, 1 and 8 rows:
+    // 12.2 and 12.7 against 12.8 and 13.2)
+    p.knt = tiles <= 256 || (MT == 1 && K <= 2560) || (M <= 8 && (tiles > 512 || K <= 5120)) ? 2 : 4;
     // with about two workgroups per compute unit four waves each (K 4096, N
     // 14336, 16 rows: 15.7 against 17.7 us with eight)
     p.ksw = p.knt == 4 && tiles > 512 && MT <= 3 ? 4 : 8;
@@ -1346,6 +1347,9 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
     // 11904, K 16896, 45 rows: 40.1 against 44.7 us; N 14144, K 25472: 75.3
     // against 64.8)
     if (MT >= 3 && K > 8192 && tiles < 768) return;
+    // nor any number from 17 rows on a longer one (N 12544, K 19456, 22 rows:
+    // 45.1 against 42.3 us)
+    if (MT >= 2 && K > 16384) return;
     p.knt = K <= 2048 && MT <= 2 ? 2 : 4;
   } else {
     // beyond 256 workgroups only where they fill whole rounds of the chip (N
