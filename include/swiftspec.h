@@ -177,9 +177,9 @@ int swiftspec_rmsnorm(const uint16_t* x, int32_t M, int32_t H, int32_t ldx, cons
  * multiplied.  Where the GEMM's plan gives each workgroup all of K and each
  * of its waves at most 2 groups of 128 (up to 16 rows, 1024 <= K <= 2048)
  * the norm runs inside the GEMM, which sums the rows' squares first and
- * forms the fp16 operand values the same way; otherwise the norm kernel
- * writes them for the GEMM.  x [M][ldx], gamma [K]
- * fp16, 16-byte aligned, ldx % 8 == 0; no residual; the workspace of
+ * forms the fp16 operand values the same way; otherwise, and where y
+ * overlaps x, the norm kernel writes them for the GEMM.  x [M][ldx],
+ * gamma [K] fp16, 16-byte aligned, ldx % 8 == 0; no residual; the workspace of
  * swiftspec_w4a16_gemm_workspace_bytes / _swiglu_workspace_bytes.  Other
  * arguments and errors as swiftspec_w4a16_gemm / _swiglu. */
 int swiftspec_rmsnorm_w4a16_gemm(const swiftspec_w4* W, const uint16_t* x, int32_t M, int32_t ldx,

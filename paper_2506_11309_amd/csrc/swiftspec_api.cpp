@@ -79,9 +79,25 @@ struct NormIn {
   float eps;
 };
 
-bool norm_in_gemm(int M, const swiftspec_w4* W0, bool swiglu) {
+// whether a row of a [M][lda] (na elements) and one of b [M][ldb] (nb) share memory
+bool rows_overlap(const uint16_t* a, int lda, int na, const uint16_t* b, int ldb, int nb, int M) {
+  const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+  const auto row = [](uintptr_t p, int ld, int m) { return p + (uintptr_t)m * ld * sizeof(uint16_t); };
+  const uintptr_t ab = (uintptr_t)na * sizeof(uint16_t), bb = (uintptr_t)nb * sizeof(uint16_t);
+  if (row(a0, lda, M - 1) + ab <= b0 || row(b0, ldb, M - 1) + bb <= a0) return false;
+  for (int i = 0; i < M; ++i)
+    for (int j = 0; j < M; ++j)
+      if (row(a0, lda, i) < row(b0, ldb, j) + bb && row(b0, ldb, j) < row(a0, lda, i) + ab) return true;
+  return false;
+}
+
+// The norm runs inside the GEMM where the plan allows it, unless y overlaps
+// x: each of the GEMM's workgroups reads all of x, with no order between one
+// workgroup's reads and another's stores to y.
+bool norm_in_gemm(const swiftspec_w4* W0, bool swiglu, const NormIn& n, int M, const uint16_t* y, int ldy) {
   ss::GemmPlan p = ss::plan_w4a16_gemm(M, W0->K, W0->N, swiglu);
-  return ss::norm_in_ksplit(p, M, W0->K, W0->N, swiglu);
+  return ss::norm_in_ksplit(p, M, W0->K, W0->N, swiglu) &&
+         !rows_overlap(n.x, n.ldx, W0->K, y, ldy, W0->N, M);
 }
 
 void run_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16_t* aprep, int M,
@@ -124,7 +140,7 @@ void run_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16_t* ap
 // the prepared operand into xprep and the GEMM reads it.
 void run_norm_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const NormIn& n, int M, uint16_t* y,
                    int ldy, uint16_t* yprep, uint16_t* xprep, void* ws, float* part, hipStream_t st) {
-  if (norm_in_gemm(M, W0, W1 != nullptr)) {
+  if (norm_in_gemm(W0, W1 != nullptr, n, M, y, ldy)) {
     run_gemm(W0, W1, nullptr, M, y, ldy, yprep, nullptr, 0, ws, part, st, &n);
   } else {
     ss::launch_rmsnorm(n.x, M, W0->K, n.ldx, n.gamma, n.eps, nullptr, 0, xprep, st);

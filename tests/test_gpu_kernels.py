@@ -484,6 +484,47 @@ def test_rmsnorm_then_projection_matches_oracle(M, K, N, ldx, swiglu):
     assert np.all(diff <= 5e-4 + 1e-3 * np.abs(chain)), diff.max()
 
 
+@pytest.mark.parametrize("M,K,N,ldx,swiglu", [(16, 1024, 1024, 1024, False), (16, 1024, 16384, 16384, False),
+                                              (13, 2048, 2048, 2056, False), (16, 1536, 8192, 8192, True)])
+def test_rmsnorm_projection_in_place(M, K, N, ldx, swiglu):
+    """y in the memory of x: the norm kernel reads x before the GEMM writes,
+    so the result is that of the norm kernel followed by the plain entry
+    point bit for bit (the norm inside the GEMM, where one workgroup would
+    store to y while another still reads x, sums the squares in another
+    order).  Rows side by side in one buffer do not overlap."""
+    x = gen.normal_f16(91, M, (M, ldx), 0.0, 2.0)
+    gamma = gen.normal_f16(92, 1, (K,), 1.0, 0.2)
+    W, Wu = _rand_w4(93, N, K), _rand_w4(94, N, K)
+    t, d = upload_w4(W)
+    tu, du = upload_w4(Wu)
+    size = ss.swiglu_workspace_bytes if swiglu else ss.gemm_workspace_bytes
+    ws = ss.workspace(size(M, K, N), dev())
+    dg = up(gamma)
+
+    def fused(buf, y):
+        if swiglu:
+            ss.rmsnorm_w4a16_swiglu(d, du, buf[:, :K], dg, y, ws)
+        else:
+            ss.rmsnorm_w4a16_gemm(d, buf[:, :K], dg, y, ws)
+        torch.cuda.synchronize()
+        return down16(y)
+
+    xn, chain = torch.zeros((M, K), dtype=torch.int16, device=dev()), torch.zeros((M, N), dtype=torch.int16, device=dev())
+    ss.rmsnorm(up(x)[:, :K], dg, xn)
+    if swiglu:
+        ss.w4a16_swiglu(d, du, xn, chain, ws)
+    else:
+        ss.w4a16_gemm(d, xn, chain, ws)
+    torch.cuda.synchronize()
+    buf = up(x)
+    assert np.array_equal(fused(buf, buf[:, :N]), down16(chain))
+    apart = fused(up(x), torch.zeros((M, N), dtype=torch.int16, device=dev()))
+    wide = torch.zeros((M, ldx + N), dtype=torch.int16, device=dev())
+    wide[:, :ldx] = up(x)
+    assert np.array_equal(fused(wide, wide[:, ldx:]), apart)
+    assert np.array_equal(down16(wide[:, :ldx]), x)
+
+
 @pytest.mark.parametrize("M,K,N", [(1, 1024, 1024), (8, 2048, 512), (13, 1024, 2048), (32, 8192, 1024),
                                    (40, 4096, 1024), (64, 2048, 1024)])
 def test_w4a16_gemm_valu_variant_matches_oracle(M, K, N):
