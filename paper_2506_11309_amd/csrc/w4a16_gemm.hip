@@ -1454,8 +1454,8 @@ GemmPlan plan_w4a16_gemm(int M, int K, int N, bool swiglu) {
   p.nwg = (int)(units < cap ? units : cap);
   const int col_w = swiglu ? p.nw / 2 : p.nw;
   const int src = swiglu ? 2 : 1;
-  // a K-split plan writes no partials
-  p.part_bytes = p.ksw ? 0 : (size_t)p.nwg * 2 * 4 * MT * col_w * src * kWave * 16;
+  // K-split workgroups and whole N-blocks write no partials
+  p.part_bytes = p.ksw || p.nblocks % p.nwg == 0 ? 0 : (size_t)p.nwg * 2 * 4 * MT * col_w * src * kWave * 16;
   p.prep_bytes = (size_t)MT * (K / 128) * 4 * kWave * 16;
   plan_wide(MT, K, tiles, swiglu, p);
   return p;

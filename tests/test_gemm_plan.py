@@ -1,0 +1,58 @@
+"""CPU checks of the W4A16 GEMM plans: workspace sizes, and the form that each
+shape of the GPU tests takes."""
+import ctypes
+import os
+
+import pytest
+
+
+class Plan(ctypes.Structure):
+    """ss::GemmPlan (ss_internal.h)."""
+    _fields_ = [("nw", ctypes.c_int), ("nblocks", ctypes.c_int), ("nwg", ctypes.c_int), ("ksw", ctypes.c_int),
+                ("knt", ctypes.c_int), ("wide", ctypes.c_bool), ("part_bytes", ctypes.c_size_t),
+                ("prep_bytes", ctypes.c_size_t)]
+
+
+@pytest.fixture(scope="module")
+def ss():
+    import paper_2506_11309_amd as ss
+    if not os.path.exists(ss.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    ss.lib()
+    return ss
+
+
+@pytest.fixture(scope="module")
+def plan(ss):
+    """plan(M, K, N, swiglu): the library's own plan of a GEMM (an internal
+    C++ function of the shared library)."""
+    f = ctypes.CDLL(ss.LIB_PATH)["_ZN2ss15plan_w4a16_gemmEiiib"]
+    f.restype = Plan
+    f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_bool]
+    return f
+
+
+# rows (every number of 16-row tiles, first and last), K and N over the range of the plan's lines
+ROWS = (1, 8, 9, 16, 17, 32, 33, 48, 49, 64)
+KS = tuple(range(128, 4096, 384)) + tuple(range(4096, 29000, 1536)) + (28672,)
+NS = tuple(range(64, 2048, 192)) + tuple(range(2048, 36000, 1088)) + (36736,)
+
+
+def test_plans_without_partials_ask_for_none(ss, plan):
+    """K-split workgroups, and N-blocks that no two workgroups share, write no
+    partial sums: the workspace holds the header and the prepared activations
+    (as it did for SwiGLUs of many columns at up to 8 rows when they had
+    K-split workgroups)."""
+    assert ss.swiglu_workspace_bytes(8, 1024, 32960) == ss.WS_HEADER_BYTES + 16 * 1024 * 2
+    seen = set()
+    for swiglu in (False, True):
+        size = ss.swiglu_workspace_bytes if swiglu else ss.gemm_workspace_bytes
+        for K in KS:
+            for N in NS:
+                for M in ROWS:
+                    p = plan(M, K, N, swiglu)
+                    if not p.wide and (p.ksw or p.nblocks % p.nwg == 0):
+                        seen.add((swiglu, p.ksw > 0))
+                        assert size(M, K, N) == ss.WS_HEADER_BYTES + ss.prepared_bytes(M, K), (M, K, N, swiglu)
+    assert seen == {(False, True), (True, True), (True, False)}
