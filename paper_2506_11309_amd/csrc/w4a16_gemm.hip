@@ -1371,7 +1371,7 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
 // round would stay under 200 workgroups (144 with S = 1, which needs no
 // partials) keep the other forms.
 static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
-  if (MT < 2 || K % (128 * kWideStep)) return;
+  if (MT < 2 || tiles < 1 || K % (128 * kWideStep)) return;
   const int nb = (tiles + (swiglu ? 8 : 16) - 1) / (swiglu ? 8 : 16);
   const int ranges = K / (128 * kWideStep), fill = 256 / nb;
   const int S = fill < ranges ? fill : ranges;
@@ -1455,7 +1455,7 @@ GemmPlan plan_w4a16_gemm(int M, int K, int N, bool swiglu) {
   const int col_w = swiglu ? p.nw / 2 : p.nw;
   const int src = swiglu ? 2 : 1;
   // K-split workgroups and whole N-blocks write no partials
-  p.part_bytes = p.ksw || p.nblocks % p.nwg == 0 ? 0 : (size_t)p.nwg * 2 * 4 * MT * col_w * src * kWave * 16;
+  p.part_bytes = p.ksw || p.nwg < 1 || p.nblocks % p.nwg == 0 ? 0 : (size_t)p.nwg * 2 * 4 * MT * col_w * src * kWave * 16;
   p.prep_bytes = (size_t)MT * (K / 128) * 4 * kWave * 16;
   plan_wide(MT, K, tiles, swiglu, p);
   return p;

@@ -56,3 +56,15 @@ def test_plans_without_partials_ask_for_none(ss, plan):
                         seen.add((swiglu, p.ksw > 0))
                         assert size(M, K, N) == ss.WS_HEADER_BYTES + ss.prepared_bytes(M, K), (M, K, N, swiglu)
     assert seen == {(False, True), (True, True), (True, False)}
+
+
+def test_size_queries_of_impossible_shapes_answer(ss):
+    """Dimensions that the calls refuse (an empty FFN, fewer columns than a
+    block) get a size from the queries, whatever the number of rows."""
+    for T in (1, 17, 33, 64):
+        for H, F in ((4096, 0), (4096, 32), (64, 4096), (0, 0)):
+            assert ss.verify_layer_workspace_bytes(ss.make_dims(H, 32, 8, 128, F, 4096), T) >= ss.WS_HEADER_BYTES
+        for K in (128, 4096, 16384, 28672):
+            for N in (16, 48):
+                assert ss.gemm_workspace_bytes(T, K, N) >= ss.WS_HEADER_BYTES
+                assert ss.swiglu_workspace_bytes(T, K, N) >= ss.WS_HEADER_BYTES
