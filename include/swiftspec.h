@@ -33,7 +33,9 @@
  *     graph.  Host-side argument checks happen before any launch; on error
  *     nothing is launched.
  *   - Scratch memory is a caller-provided device workspace whose size comes
- *     from the matching *_workspace_bytes query.  The first
+ *     from the matching *_workspace_bytes query, for the sizes of the call
+ *     (those of the W4A16 GEMMs, verify_layer and verify_step also serve
+ *     fewer rows or tree nodes).  The first
  *     SWIFTSPEC_WS_HEADER_BYTES bytes of every workspace hold an error word
  *     and reserved words that must be zero before first use (allocate it
  *     zero-filled or call swiftspec_workspace_init once); every call leaves

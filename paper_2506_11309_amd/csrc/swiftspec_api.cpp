@@ -64,9 +64,22 @@ bool attn_counters_fit(int T, int Hq, int Hkv) {
   return (long)Hkv * ((R + 63) / 64) <= kMaxCounters;
 }
 
+// what a GEMM of M rows needs
 size_t gemm_ws(int M, int K, int N, bool swiglu) {
   ss::GemmPlan p = ss::plan_w4a16_gemm(M, K, N, swiglu);
   return kHeader + align_up(p.prep_bytes) + align_up(p.part_bytes);
+}
+
+// what the size query answers: the largest need of up to M rows, as a caller
+// with trees of changing size allocates once for the largest (the forms of
+// fewer rows may write more partial sums)
+size_t gemm_ws_query(int M, int K, int N, bool swiglu) {
+  size_t most = gemm_ws(M, K, N, swiglu);
+  for (int m = 16; m < M && m < SWIFTSPEC_MAX_M; m += 16) {
+    const size_t b = gemm_ws(m, K, N, swiglu);
+    most = b > most ? b : most;
+  }
+  return most;
 }
 
 // Launch a validated W4A16 GEMM / SwiGLU reading prepared activations.
@@ -286,6 +299,18 @@ LayerWs layer_ws(const swiftspec_dims* d, int T) {
   return w;
 }
 
+// The layer's size query: the largest need of trees of up to T nodes (the
+// GEMMs' as above; the attention's prefix splits follow the row count, so
+// the partials of a smaller tree may be larger too).
+size_t layer_ws_query(const swiftspec_dims* d, int T) {
+  size_t most = 0;
+  for (int t = 1; t <= T; ++t) {
+    const size_t b = layer_ws(d, t).total;
+    most = b > most ? b : most;
+  }
+  return most;
+}
+
 }  // namespace
 
 extern "C" {
@@ -348,12 +373,12 @@ int swiftspec_w4_prepack(const swiftspec_w4* W, void* packed, size_t packed_byte
 
 size_t swiftspec_w4a16_gemm_workspace_bytes(int32_t M, int32_t K, int32_t N) {
   if (M < 1 || K < 128 || N < 16) return kHeader;
-  return gemm_ws(M, K, N, false);
+  return gemm_ws_query(M, K, N, false);
 }
 
 size_t swiftspec_w4a16_swiglu_workspace_bytes(int32_t M, int32_t K, int32_t N) {
   if (M < 1 || K < 128 || N < 16) return kHeader;
-  return gemm_ws(M, K, N, true);
+  return gemm_ws_query(M, K, N, true);
 }
 
 int swiftspec_w4a16_gemm(const swiftspec_w4* W, const uint16_t* x, int32_t M, int32_t ldx,
@@ -706,7 +731,7 @@ int swiftspec_topk_logprobs(const uint16_t* logits, int32_t ldl, int32_t n, int3
 
 size_t swiftspec_verify_layer_workspace_bytes(const swiftspec_dims* dims, int32_t T) {
   if (!dims || T < 1 || T > SWIFTSPEC_MAX_TREE) return kHeader;
-  return layer_ws(dims, T).total;
+  return layer_ws_query(dims, T);
 }
 
 int swiftspec_verify_layer_workspace_layout(const swiftspec_dims* dims, int32_t T, size_t* offsets) {
@@ -777,7 +802,7 @@ int swiftspec_verify_layer(const swiftspec_layer* Lw, const swiftspec_dims* d, u
 
 size_t swiftspec_verify_step_workspace_bytes(const swiftspec_dims* dims, int32_t T, int32_t V) {
   if (!dims || T < 1 || T > SWIFTSPEC_MAX_TREE) return kHeader;
-  const size_t layer = layer_ws(dims, T).total;
+  const size_t layer = layer_ws_query(dims, T);
   const size_t head = V > 0 ? swiftspec_lm_head_workspace_bytes(T, dims->H, V) : 0;
   return layer > head ? layer : head;
 }
@@ -801,7 +826,8 @@ int swiftspec_verify_step(const swiftspec_layer* layers, int32_t n_layers, const
     if (!aligned16(final_norm) || !aligned16(lm_head)) return SWIFTSPEC_MISALIGNED;
   }
   if (!aligned16(hidden) || !aligned16(ws)) return SWIFTSPEC_MISALIGNED;
-  if (ws_bytes < swiftspec_verify_step_workspace_bytes(d, T, V)) return SWIFTSPEC_WORKSPACE_TOO_SMALL;
+  if (ws_bytes < layer_ws(d, T).total || (V > 0 && ws_bytes < swiftspec_lm_head_workspace_bytes(T, d->H, V)))
+    return SWIFTSPEC_WORKSPACE_TOO_SMALL;
   hipStream_t st = S(stream);
   for (int l = 0; l < n_layers; ++l) enqueue_layer(&layers[l], d, hidden, T, d_prefix_len, d_parent, rope, ws, st);
   if (V > 0) {

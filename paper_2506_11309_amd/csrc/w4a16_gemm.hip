@@ -1382,8 +1382,7 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
     // 45 rows 16.6 -> 16.1 us; K 4608, N 19136, 64 rows 45.2 -> 39.3); below
     // that, above 32 rows, a K long enough for two or three ranges (K 6144, N
     // 16256, 64 rows 44.2 -> 38.7; K 4608, N 13568 32.7 -> 31.1; K 3584, N
-    // 14208 27.8 -> 28.3; up to 32 rows the K-split form, which asks for no
-    // partials, keeps its workspaces)
+    // 14208 27.8 -> 28.3)
     if (tiles <= 1088 && (tiles <= 512 || MT < 3 || K < 4608)) return;
     // up to 32 rows only a long K (weights read again from the Infinity
     // Cache: K 3072, N 21120, 29 rows 21.8 -> 23.8 us; K 4608, N 19136, 20
@@ -1402,10 +1401,7 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
   p.ksw = 0;
   p.nblocks = nb;
   p.nwg = nb * S;
-  // at least what the plan it replaces asks for, so that a workspace sized
-  // for some number of rows still serves every smaller one
-  const size_t part = S > 1 ? (size_t)p.nwg * kWideW * MT * 2 * kWave * 16 : 0;
-  if (part > p.part_bytes) p.part_bytes = part;
+  p.part_bytes = S > 1 ? (size_t)p.nwg * kWideW * MT * 2 * kWave * 16 : 0;
 }
 
 // The RMSNorm runs inside a K-split GEMM where no wave then holds more than

@@ -68,3 +68,20 @@ def test_size_queries_of_impossible_shapes_answer(ss):
             for N in (16, 48):
                 assert ss.gemm_workspace_bytes(T, K, N) >= ss.WS_HEADER_BYTES
                 assert ss.swiglu_workspace_bytes(T, K, N) >= ss.WS_HEADER_BYTES
+
+
+def test_a_workspace_serves_fewer_rows(ss):
+    """A workspace sized for some number of rows (tree nodes) is large enough
+    for every smaller one, though the forms of fewer rows may write more
+    partial sums and a smaller tree's attention may have more parts."""
+    for size in (ss.gemm_workspace_bytes, ss.swiglu_workspace_bytes):
+        for K in KS:
+            for N in NS:
+                sizes = [size(M, K, N) for M in ROWS]
+                assert sizes == sorted(sizes), (size.__name__, K, N, sizes)
+    for dims in ((8192, 16, 8, 128, 15232, 128), (2560, 16, 4, 64, 10752, 600), (8192, 64, 8, 128, 28672, 4160),
+                 (4096, 32, 8, 128, 14336, 33000), (2048, 32, 8, 64, 8192, 640)):
+        d = ss.make_dims(*dims)
+        for size in (lambda T: ss.verify_layer_workspace_bytes(d, T), lambda T: ss.verify_step_workspace_bytes(d, T, 32000)):
+            sizes = [size(T) for T in range(1, ss.MAX_TREE + 1)]
+            assert sizes == sorted(sizes), dims
