@@ -1309,11 +1309,25 @@ void launch_w4a16_gemm(const GemmLaunch& L, hipStream_t st) {
   else launch_mt<EPI_PLAIN>(L, st);
 }
 
+// The longest K that one-tile K-split workgroups take above 16 rows.  nb: the
+// stream-K form's column blocks.  Above 32 rows it cuts few of them into
+// slivers and is then the slower one on a longer K too (N 1024, 40 rows: nb 8
+// and 0.82 of its time with the K split at K 16384, nb 16 and 1.26 at K 12288).
+static int ksplit_longest(int MT, int K, int tiles) {
+  const int nb = K >= 16384 && tiles % 8 == 0 ? tiles / 8 : tiles / 4;
+  if (MT == 2) return tiles <= 32 ? 20480 : tiles <= 48 ? 16384 : tiles <= 80 ? 10240 : tiles < 224 ? 8192 : 12288;
+  if (nb <= 6) return K;
+  if (nb <= 12) return nb <= 10 ? 20480 : 16384;
+  return tiles <= 80 ? 10240 : tiles < 224 ? 10240 - 1024 * MT : 24576 / MT;
+}
+
 // K-split plan (ksw waves, knt weight tiles per workgroup) of a shape, or
-// ksw = 0 for the stream-K kernel.  The lines come from sweeps over 34 plain
-// and 26 SwiGLU shapes (K 1024 .. 28672, N 1024 .. 32768) at 4, 13, 29, 45
-// and 64 rows against the kernels used before: 1.36 and 1.30 times faster
-// over the sweeps.
+// ksw = 0 for the stream-K kernel.  The lines come from both forms timed on
+// 3100 shapes (N 256 .. 49152, K 1024 .. 28672, 1 to 60 rows), the weights
+// rotated through more memory than the Infinity Cache holds, as those of a
+// model are; "times as fast" and ratios beside them are of that.  Weights
+// read again from the Infinity Cache favour the K split by a further tenth
+// to a fifth.
 static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& p) {
   const int G = K / 128;
   if (swiglu) {
@@ -1333,28 +1347,45 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
   }
   const int wg4 = (tiles + 3) / 4, rounds = (wg4 + 255) / 256;
   if (tiles <= 256) {
-    // one tile: an activation read of MT * K * 32 bytes per workgroup pays
-    // up to about 0.75 MB (N 2560, K 8192, 64 rows: 13.6 against 16 us), or
-    // where the columns are too few for the other form (N 1152, K 10368, 64
-    // rows: 21.8 against 15.7 us)
-    if (MT > 1 && MT * K > 24576 && tiles >= 128) return;
+    // one tile.  Above 16 rows few workgroups on a long K stream too little
+    // at once, and the activation read of MT * K * 32 bytes per workgroup
+    // grows: stream-K from there on (K 20992, N 1472, 36 rows 32.1 -> 20.3
+    // us; K 8192, N 1536, 60 rows 1.16 times as fast)
+    if (MT > 1 && K > ksplit_longest(MT, K, tiles)) return;
     p.knt = 1;
   } else if (tiles <= 512) {
-    if (MT > 1 && MT * K > 32768) return;  // N 8192, K 28672, 32 rows: 39.4 against 43.5 us
+    // N 8192, K 28672, 32 rows: 39.4 us with stream-K, 43.5 with the K split
+    // (weights from the Infinity Cache); above 32 rows N 4608, K 10240 1.11
+    // times as fast with stream-K
+    if (MT > 1 && MT * K > 32768) return;
+    if (MT > 2 && K > 8192 && tiles < 320) return;
     p.knt = 2;
   } else if (tiles <= 1024) {
     // above 32 rows fewer than 192 workgroups do not pay on a long K (N
     // 11904, K 16896, 45 rows: 40.1 against 44.7 us; N 14144, K 25472: 75.3
-    // against 64.8)
+    // against 64.8; weights from the Infinity Cache)
     if (MT >= 3 && K > 8192 && tiles < 768) return;
-    // nor any number from 17 rows on a longer one (N 12544, K 19456, 22 rows:
-    // 45.1 against 42.3 us)
-    if (MT >= 2 && K > 16384) return;
+    // nor any number from 17 rows on a longer one (N 9216, K 16384, 24 rows
+    // 1.12 times as fast with stream-K; N 12544, K 19456, 22 rows: 45.1
+    // against 42.3 us, weights from the Infinity Cache)
+    if (MT >= 2 && K > (tiles < 768 ? 14336 : 16384)) return;
+    // nor up to 16 rows (N 9600, K 20480, 12 rows 1.19 times as fast)
+    if (K > 16384 && tiles < 704) return;
     p.knt = K <= 2048 && MT <= 2 ? 2 : 4;
   } else {
     // beyond 256 workgroups only where they fill whole rounds of the chip (N
-    // 28992, K 27008: 107 -> 81 us at 4 rows; N 19328, K 24960: 58 -> 66)
+    // 28992, K 27008, 4 rows: 0.76 of stream-K's time; N 19328, K 24960:
+    // 58 -> 66 us, weights from the Infinity Cache), or for a short K
     if (20 * wg4 < 17 * 256 * rounds && K > 2048 && !(MT == 1 && K <= 8192)) return;
+    // not where K is a multiple of 8192, so that every tile begins at a
+    // multiple of 64 KB (4 rows, K 8192: N 16640 1.29 and N 35200 1.19 times
+    // as fast with stream-K; but N 28992, where stream-K has one tile per
+    // wave, 0.85), nor at 17 to 32 rows for a multiple of 4096 and N one of
+    // 8192 (K 4096, N 32768: 1.14)
+    if (MT == 1 && K % 8192 == 0 && (tiles % 8 == 0 || tiles < 1600)) return;
+    if (MT == 2 && K % 4096 == 0 && tiles % 512 == 0) return;
+    // nor from 17 rows on a very long K (K 27008, N 32768, 24 rows: 1.18; N 28992 0.92)
+    if (MT >= 2 && K > 16384 && tiles % 8 == 0) return;
     p.knt = K <= 2048 && MT <= 2 ? 2 : 4;
   }
   // 16 waves where one M-tile leaves the registers and K the groups (K 14336,

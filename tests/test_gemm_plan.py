@@ -41,20 +41,17 @@ NS = tuple(range(64, 2048, 192)) + tuple(range(2048, 36000, 1088)) + (36736,)
 
 def test_plans_without_partials_ask_for_none(ss, plan):
     """K-split workgroups, and N-blocks that no two workgroups share, write no
-    partial sums: the workspace holds the header and the prepared activations
-    (as it did for SwiGLUs of many columns at up to 8 rows when they had
-    K-split workgroups)."""
+    partial sums."""
     assert ss.swiglu_workspace_bytes(8, 1024, 32960) == ss.WS_HEADER_BYTES + 16 * 1024 * 2
     seen = set()
     for swiglu in (False, True):
-        size = ss.swiglu_workspace_bytes if swiglu else ss.gemm_workspace_bytes
         for K in KS:
             for N in NS:
                 for M in ROWS:
                     p = plan(M, K, N, swiglu)
                     if not p.wide and (p.ksw or p.nblocks % p.nwg == 0):
                         seen.add((swiglu, p.ksw > 0))
-                        assert size(M, K, N) == ss.WS_HEADER_BYTES + ss.prepared_bytes(M, K), (M, K, N, swiglu)
+                        assert p.part_bytes == 0, (M, K, N, swiglu)
     assert seen == {(False, True), (True, True), (True, False)}
 
 
@@ -85,3 +82,32 @@ def test_a_workspace_serves_fewer_rows(ss):
         for size in (lambda T: ss.verify_layer_workspace_bytes(d, T), lambda T: ss.verify_step_workspace_bytes(d, T, 32000)):
             sizes = [size(T) for T in range(1, ss.MAX_TREE + 1)]
             assert sizes == sorted(sizes), dims
+
+
+def _form(p):
+    return "wide" if p.wide else "K-split" if p.ksw else "stream-K"
+
+
+# Both sides of the plan's lines, with the time of the K-split form over that
+# of stream-K, weights from HBM.
+@pytest.mark.parametrize("M,K,N,form", [
+    # few columns, 17 rows and more: 0.77, 1.16; 0.91, 1.10; 0.97, 1.09
+    (24, 8192, 1024, "K-split"), (24, 12288, 1024, "stream-K"), (24, 16384, 768, "K-split"), (24, 20480, 768, "stream-K"),
+    (24, 8192, 1536, "K-split"), (24, 10240, 1536, "stream-K"),
+    # 0.84, 1.04; 0.90, 1.26; 0.82 (fewer stream-K blocks from K 16384); 0.94 at any K
+    (40, 7168, 1536, "K-split"), (40, 8192, 1536, "stream-K"), (40, 10240, 1024, "K-split"), (40, 12288, 1024, "stream-K"),
+    (40, 16384, 1024, "K-split"), (40, 28672, 768, "K-split"),
+    # 0.77, 1.16; 1.46; 0.96, 1.10
+    (60, 6144, 1536, "K-split"), (60, 8192, 1536, "stream-K"), (60, 12288, 1024, "stream-K"), (60, 6144, 2048, "K-split"),
+    (60, 7168, 2048, "stream-K"),
+    # 0.97, 1.10; 0.99; 1.00, 1.10
+    (40, 8192, 4608, "K-split"), (40, 10240, 4608, "stream-K"), (40, 10240, 6144, "K-split"),
+    (24, 14336, 9216, "K-split"), (24, 16384, 9216, "stream-K"),
+    # up to 16 rows: 1.02, 1.14; 0.95
+    (12, 16384, 9600, "K-split"), (12, 20480, 9600, "stream-K"), (12, 20480, 11264, "K-split"),
+    # more than 1024 column tiles: 0.90, 1.27; 0.83, 1.04; 1.18; 0.96, 1.14; 1.08, 0.89
+    (4, 7168, 16640, "K-split"), (4, 8192, 16640, "stream-K"), (4, 8192, 28992, "K-split"), (4, 8192, 28800, "stream-K"),
+    (4, 8192, 35200, "stream-K"), (24, 4096, 28800, "K-split"), (24, 4096, 32768, "stream-K"),
+    (24, 27008, 28800, "stream-K"), (24, 27008, 28992, "K-split")])
+def test_plain_lines_with_weights_from_hbm(plan, M, K, N, form):
+    assert _form(plan(M, K, N, False)) == form
