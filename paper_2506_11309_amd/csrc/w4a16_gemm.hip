@@ -1332,6 +1332,13 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
   const int G = K / 128;
   if (swiglu) {
     if (tiles > 1088) return;  // more column tiles: the stream-K form's shared activations win (N 28672: 60 against 64 us at 32 rows)
+    // few column tiles on a long K, as for the plain form below (K 27264, N
+    // 1088, 59 rows 56.1 -> 33.0 us with stream-K; K 12288, N 2048 1.05 and
+    // 1.12 times as fast at 40 and 60 rows; K 28672, N 6144 1.10 at 14 rows)
+    if (tiles < 448) {
+      if (MT >= 3 && tiles > 16 && K > (tiles <= 32 ? 16384 : tiles <= 160 ? 10240 : 12288)) return;
+      if (M > 8 && tiles > 48 && K > 24576) return;
+    }
     // above 32 rows at more than one workgroup per compute unit only for a
     // short K (K 5888, N 10816, 64 rows: 34.5 against 36.4 us)
     if (tiles > 512 && MT >= 3 && (K > 4096 || tiles > 1024)) return;

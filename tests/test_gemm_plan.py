@@ -111,3 +111,15 @@ def _form(p):
     (24, 27008, 28800, "stream-K"), (24, 27008, 28992, "K-split")])
 def test_plain_lines_with_weights_from_hbm(plan, M, K, N, form):
     assert _form(plan(M, K, N, False)) == form
+
+
+@pytest.mark.parametrize("M,K,N,form", [
+    # up to 8 rows any K; above: 0.98, 1.10; 1.08 at 24 rows
+    (8, 28672, 6144, "K-split"), (14, 20480, 6144, "K-split"), (14, 28672, 6144, "stream-K"),
+    (24, 20480, 1024, "K-split"), (24, 28672, 1024, "stream-K"),
+    # above 32 rows: 0.95, 1.05; 1.12 at 60; 0.91, 1.01 .. 1.13; 0.98, 1.10; up to 256 columns any K: 0.80
+    (40, 10240, 2048, "K-split"), (40, 12288, 2048, "stream-K"), (60, 12288, 2048, "stream-K"),
+    (40, 16384, 512, "K-split"), (60, 20480, 512, "stream-K"), (40, 12288, 5120, "K-split"), (60, 16384, 5120, "stream-K"),
+    (40, 28672, 256, "K-split"), (40, 28672, 7168, "K-split")])
+def test_swiglu_lines_with_weights_from_hbm(plan, M, K, N, form):
+    assert _form(plan(M, K, N, True)) == form
