@@ -1331,7 +1331,11 @@ static int ksplit_longest(int MT, int K, int tiles) {
 static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& p) {
   const int G = K / 128;
   if (swiglu) {
-    if (tiles > 1088) return;  // more column tiles: the stream-K form's shared activations win (N 28672: 60 against 64 us at 32 rows)
+    // more column tiles: the stream-K form's shared activations win (N 28672:
+    // 60 against 64 us at 32 rows), but not at up to 8 rows over a short K (1
+    // row, N 17664: K 1536 0.79, K 3072 0.80, K 4096 0.82 of stream-K's time;
+    // N 24576 0.95, 0.90, 0.93; N 28672 1.04, 0.98, 1.01)
+    if (tiles > 1088 && (M > 8 || tiles > 1536 || K > 4096)) return;
     // few column tiles on a long K, as for the plain form below (K 27264, N
     // 1088, 59 rows 56.1 -> 33.0 us with stream-K; K 12288, N 2048 1.05 and
     // 1.12 times as fast at 40 and 60 rows; K 28672, N 6144 1.10 at 14 rows)

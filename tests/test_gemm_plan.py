@@ -120,6 +120,9 @@ def test_plain_lines_with_weights_from_hbm(plan, M, K, N, form):
     # above 32 rows: 0.95, 1.05; 1.12 at 60; 0.91, 1.01 .. 1.13; 0.98, 1.10; up to 256 columns any K: 0.80
     (40, 10240, 2048, "K-split"), (40, 12288, 2048, "stream-K"), (60, 12288, 2048, "stream-K"),
     (40, 16384, 512, "K-split"), (60, 20480, 512, "stream-K"), (40, 12288, 5120, "K-split"), (60, 16384, 5120, "stream-K"),
-    (40, 28672, 256, "K-split"), (40, 28672, 7168, "K-split")])
+    (40, 28672, 256, "K-split"), (40, 28672, 7168, "K-split"),
+    # more than 1088 column tiles, up to 8 rows: 0.80, 0.82; 0.89; 1.0
+    (1, 3072, 17664, "K-split"), (8, 4096, 19200, "K-split"), (8, 1536, 24576, "K-split"), (8, 2048, 28672, "stream-K"),
+    (8, 4224, 17664, "stream-K"), (9, 3072, 17664, "stream-K")])
 def test_swiglu_lines_with_weights_from_hbm(plan, M, K, N, form):
     assert _form(plan(M, K, N, True)) == form

@@ -380,7 +380,9 @@ def test_w4a16_swiglu_two_column_blocks(M, K, N):
     (7, 2176, 8256, False), (49, 2176, 8256, False), (32, 1024, 8256, False),
     # SwiGLU: gate and up of one column tile; of two, with 8 and with 4 waves
     (16, 256, 448, True), (64, 1408, 1088, True), (31, 2688, 4160, True), (64, 2688, 4160, True),
-    (9, 2688, 8256, True), (48, 2688, 8256, True), (64, 4096, 8256, True)])
+    (9, 2688, 8256, True), (48, 2688, 8256, True), (64, 4096, 8256, True),
+    # more than 1088 column tiles at up to 8 rows
+    (8, 2944, 20928, True), (1, 1152, 24576, True)])
 def test_w4a16_k_split_forms(M, K, N, swiglu):
     """The K-split workgroups at the edges of their plan: waves without a
     group, uneven group ranges, every number of M-tiles and of weight tiles
