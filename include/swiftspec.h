@@ -176,8 +176,8 @@ int swiftspec_rmsnorm(const uint16_t* x, int32_t M, int32_t H, int32_t ldx, cons
  *   swiftspec_rmsnorm_w4a16_swiglu: y = fp16( silu(xn . Wg'^T) * (xn . Wu'^T) )
  * with xn[m] = x[m] / sqrt(mean_k x[m][k]^2 + eps) * gamma over the K
  * columns, xn rounded to fp16 (as swiftspec_rmsnorm computes it) and then
- * multiplied.  Where the GEMM's plan gives each workgroup all of K and each
- * of its waves at most 2 groups of 128 (up to 16 rows, 1024 <= K <= 2048)
+ * multiplied.  Where the GEMM's plan gives each workgroup all of K and K is
+ * short enough for its registers (up to 16 rows, 1024 <= K <= 2048)
  * the norm runs inside the GEMM, which sums the rows' squares first and
  * forms the fp16 operand values the same way; otherwise, and where y
  * overlaps x, the norm kernel writes them for the GEMM.  x [M][ldx],

@@ -35,10 +35,6 @@ struct GemmLaunch {
   float* part;  // split-K partial slots (2 per workgroup)
 };
 
-// A K-split GEMM applies the RMSNorm of its input itself where no wave
-// holds more than this many 128-wide groups (all its loads in registers).
-constexpr int kNormGroupsPerWave = 2;
-
 struct GemmPlan {
   int nw, nblocks, nwg, ksw = 0, knt = 0;
   bool wide = false;

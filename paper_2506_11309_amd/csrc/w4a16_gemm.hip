@@ -958,8 +958,8 @@ __global__ __launch_bounds__(64 * W) void w4a16_ksplit_kernel(GemmArgs a) {
 // ------------------------------------------- small M, RMSNorm in the GEMM
 // The QKV projection and the fused SwiGLU read the RMSNorm of the residual
 // stream (the decoder layer of Sec. 2).  Where K-split workgroups give each
-// wave at most two groups (norm_in_ksplit), the workgroup (which reads all
-// of K anyway) normalises the plain rows x itself: every wave issues all its
+// wave at most NG = 2 or 4 groups (norm_in_ksplit), the workgroup (which reads
+// all of K anyway) normalises the plain rows x itself: every wave issues all its
 // loads up front (the row chunks of its groups, gamma, then the weight
 // blocks, so that the row sums wait for the row chunks only), sums x^2
 // over its groups, the waves' sums meet in LDS,
@@ -973,10 +973,10 @@ __global__ __launch_bounds__(64 * W) void w4a16_ksplit_kernel(GemmArgs a) {
 // 1B-shaped QKV, one of 4 KB + 128 B no faster): load f of row r takes the
 // 16-byte chunk f ^ (r & 3) and two rounds of bitwise lane selects put the
 // chunks back in order.
-template <int W, int NT, bool SW>
+template <int W, int NT, bool SW, int NG>
 __global__ __launch_bounds__(64 * W) void w4a16_ksplit_norm_kernel(GemmArgs a) {
   constexpr int kC = SW ? NT / 2 : NT;  // output column tiles of the workgroup
-  constexpr int NG = kNormGroupsPerWave;
+  static_assert(NG <= 4, "gam holds 16 chunks of 4 groups");
   __shared__ f32x4 red[W][NT][kWave];
   __shared__ float red_ss[W][16];
   __shared__ u32x4 gam[W][kWave];
@@ -1269,9 +1269,9 @@ static void launch_ks_mt(const GemmLaunch& L, hipStream_t st) {
   }
   launch_ks<W, 1, NT, SW>(L, st);
 }
-template <int W, int NT, bool SW>
+template <int W, int NT, bool SW, int NG = 2>
 static void launch_ksn(const GemmLaunch& L, hipStream_t st) {
-  hipLaunchKernelGGL((w4a16_ksplit_norm_kernel<W, NT, SW>), dim3(L.N / 16 / (SW ? NT / 2 : NT)), dim3(64 * W), 0, st,
+  hipLaunchKernelGGL((w4a16_ksplit_norm_kernel<W, NT, SW, NG>), dim3(L.N / 16 / (SW ? NT / 2 : NT)), dim3(64 * W), 0, st,
                      gemm_args(L));
 }
 
@@ -1282,8 +1282,9 @@ void launch_w4a16_gemm(const GemmLaunch& L, hipStream_t st) {
   }
   if (L.ksw && L.xnorm) {
     if (L.swiglu) {
-      if (L.ksw == 8) L.knt == 2 ? launch_ksn<8, 2, true>(L, st) : launch_ksn<8, 4, true>(L, st);
-      else L.knt == 2 ? launch_ksn<4, 2, true>(L, st) : launch_ksn<4, 4, true>(L, st);
+      if (L.ksw == 8) launch_ksn<8, 4, true>(L, st);
+      else if (L.K <= 1024) L.knt == 2 ? launch_ksn<4, 2, true>(L, st) : launch_ksn<4, 4, true>(L, st);
+      else L.knt == 2 ? launch_ksn<4, 2, true, 4>(L, st) : launch_ksn<4, 4, true, 4>(L, st);
     } else if (L.ksw == 8) {
       L.knt == 1 ? launch_ksn<8, 1, false>(L, st) : L.knt == 2 ? launch_ksn<8, 2, false>(L, st) : launch_ksn<8, 4, false>(L, st);
     } else {
@@ -1446,17 +1447,26 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
   p.part_bytes = S > 1 ? (size_t)p.nwg * kWideW * MT * 2 * kWave * 16 : 0;
 }
 
-// The RMSNorm runs inside a K-split GEMM where no wave then holds more than
-// two groups (up to 2048 wide, one M-tile): every workgroup normalises all
+// The RMSNorm runs inside a K-split GEMM where a workgroup holds all of K in
+// registers (1024 <= K <= 2048, one M-tile): every workgroup normalises all
 // of K for itself, so it pays while that is short (K 2048, N 3072, 8 rows:
 // 5.4 us against 6.6 with the norm kernel; at K 3072 and 4096 within 0.3 us
-// of it either way, and slower at N >= 10240).
+// of it either way, and slower at N >= 10240).  A SwiGLU has four waves of up
+// to four groups where a workgroup's column is one tile or K at most 1536
+// (8 rows, weights from HBM: K 1280, N 2048 1.09 times as fast as eight waves
+// of two groups, N 8192 1.07; K 2048, N 8192 0.97), and one tile up to one
+// workgroup per compute unit or where two would leave a second round nearly
+// empty (N 10240: K 1280 1.17, K 2048 1.04 times as fast).
 bool norm_in_ksplit(GemmPlan& p, int M, int K, int N, bool swiglu) {
   const int G = K / 128, tiles = N / 16;
   if (!p.ksw || M > 16 || G < 8 || G > 16) return false;
-  p.ksw = G <= 8 ? 4 : 8;
-  if (swiglu) p.knt = tiles <= 256 ? 2 : 4;
-  else p.knt = tiles <= 256 ? 1 : tiles <= 512 ? 2 : 4;
+  if (swiglu) {
+    p.knt = tiles <= 256 || (tiles > 512 && tiles <= 832) ? 2 : 4;
+    p.ksw = p.knt == 2 || G <= 12 ? 4 : 8;
+  } else {
+    p.knt = tiles <= 256 ? 1 : tiles <= 512 ? 2 : 4;
+    p.ksw = G <= 8 ? 4 : 8;
+  }
   return true;
 }
 

@@ -33,6 +33,16 @@ def plan(ss):
     return f
 
 
+@pytest.fixture(scope="module")
+def norm(ss):
+    """norm(plan, M, K, N, swiglu): whether the GEMM of that plan applies the
+    RMSNorm of its input itself (the plan is then changed to that form's)."""
+    f = ctypes.CDLL(ss.LIB_PATH)["_ZN2ss14norm_in_ksplitERNS_8GemmPlanEiiib"]
+    f.restype = ctypes.c_bool
+    f.argtypes = [ctypes.POINTER(Plan), ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_bool]
+    return lambda p, M, K, N, swiglu: f(ctypes.byref(p), M, K, N, swiglu)
+
+
 # rows (every number of 16-row tiles, first and last), K and N over the range of the plan's lines
 ROWS = (1, 8, 9, 16, 17, 32, 33, 48, 49, 64)
 KS = tuple(range(128, 4096, 384)) + tuple(range(4096, 29000, 1536)) + (28672,)
@@ -126,3 +136,16 @@ def test_plain_lines_with_weights_from_hbm(plan, M, K, N, form):
     (8, 4224, 17664, "stream-K"), (9, 3072, 17664, "stream-K")])
 def test_swiglu_lines_with_weights_from_hbm(plan, M, K, N, form):
     assert _form(plan(M, K, N, True)) == form
+
+
+@pytest.mark.parametrize("K,N,waves,tiles", [
+    (1024, 4096, 4, 2), (2048, 4096, 4, 2), (1280, 8192, 4, 4), (1536, 8192, 4, 4), (2048, 8192, 8, 4),
+    (1280, 10240, 4, 2), (2048, 13312, 4, 2), (2048, 13376, 8, 4), (1536, 17408, 4, 4)])
+def test_swiglu_with_norm_has_four_waves(plan, norm, K, N, waves, tiles):
+    """The RMSNorm inside the SwiGLU: four waves where a workgroup's column is
+    one tile (gate and up: 2) or K is at most 1536 (time over the present one
+    with eight waves, weights from HBM, 8 rows: K 1280, N 2048 1.09, N 8192
+    1.07, N 10240 1.17)."""
+    for M in (1, 8, 16):
+        p = plan(M, K, N, True)
+        assert norm(p, M, K, N, True) and (p.ksw, p.knt) == (waves, tiles)
