@@ -1438,6 +1438,10 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
     // only many columns: K 12288, N 18432 40.1 -> 38.4, K 8192, N 21184 32.4
     // -> 31.4; K 28672, N 8192 40.8 -> 41.1, K 20480, N 5952 25.1 -> 27.0
     if (MT == 2 && tiles <= 1024) return;
+    // and there only over two or more K ranges, as one leaves up to 112 units
+    // idle (K 12288, 24 rows: N 36864 1.16, N 49152 1.15 times as fast with
+    // stream-K, weights from HBM)
+    if (MT == 2 && S < 2) return;
     if (K < 8192 || tiles <= 256 || kn < (K >= 16384 ? 1.0e8 : 1.4e8)) return;
   }
   p.wide = true;

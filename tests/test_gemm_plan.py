@@ -118,7 +118,9 @@ def _form(p):
     # more than 1024 column tiles: 0.90, 1.27; 0.83, 1.04; 1.18; 0.96, 1.14; 1.08, 0.89
     (4, 7168, 16640, "K-split"), (4, 8192, 16640, "stream-K"), (4, 8192, 28992, "K-split"), (4, 8192, 28800, "stream-K"),
     (4, 8192, 35200, "stream-K"), (24, 4096, 28800, "K-split"), (24, 4096, 32768, "stream-K"),
-    (24, 27008, 28800, "stream-K"), (24, 27008, 28992, "K-split")])
+    (24, 27008, 28800, "stream-K"), (24, 27008, 28992, "K-split"),
+    # one K range of wide blocks at 17 to 32 rows 1.15 of stream-K, above 0.9
+    (24, 12288, 32768, "wide"), (24, 12288, 36864, "stream-K"), (40, 12288, 49152, "wide")])
 def test_plain_lines_with_weights_from_hbm(plan, M, K, N, form):
     assert _form(plan(M, K, N, False)) == form
 
