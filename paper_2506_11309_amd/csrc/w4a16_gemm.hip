@@ -1427,18 +1427,22 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
     // 16256, 64 rows 44.2 -> 38.7; K 4608, N 13568 32.7 -> 31.1; K 3584, N
     // 14208 27.8 -> 28.3)
     if (tiles <= 1088 && (tiles <= 512 || MT < 3 || K < 4608)) return;
-    // up to 32 rows only a long K (weights read again from the Infinity
-    // Cache: K 3072, N 21120, 29 rows 21.8 -> 23.8 us; K 4608, N 19136, 20
-    // rows 31.6 -> 32.7; K 8192, N 22528, 29 rows 56.7 -> 54.4)
+    // up to 32 rows only a long K (weights from HBM: K 1536 1.02 .. 1.06 of
+    // stream-K's time, K 3072 0.98 .. 1.04, K 4608 .. 7168 0.9 .. 1.0, K 8192
+    // 0.88 .. 0.98; from the Infinity Cache 1.04 .. 1.1 at any K: K 8192, N
+    // 28672, 32 rows 57.9 -> 55.8 and 47.1 -> 51.5 us)
     if (MT == 2 && K < 8192) return;
   } else {
     // above 32 rows K 8192, N 21184 39.7 -> 36.7 us (45 rows); K 20480, N
     // 5952 36.3 -> 34.8 (64); K 28672, N 8192 54.8 -> 51.0 (64); not K 8192, N
-    // 10240 (27.7 -> 27.4) or K 14336, N 4096 (25.3 -> 26.2).  Up to 32 rows
-    // only many columns: K 12288, N 18432 40.1 -> 38.4, K 8192, N 21184 32.4
-    // -> 31.4; K 28672, N 8192 40.8 -> 41.1, K 20480, N 5952 25.1 -> 27.0
-    if (MT == 2 && tiles <= 1024) return;
-    // and there only over two or more K ranges, as one leaves up to 112 units
+    // 10240 (27.7 -> 27.4) or K 14336, N 4096 (25.3 -> 26.2) (weights from the
+    // Infinity Cache).  Up to 32 rows, weights from HBM, where the K split
+    // stops and the columns suffice: K 28672, N 8192, 32 rows 39.9 -> 36.1 us
+    // (from the Infinity Cache 31.3 -> 32.8), K 18432, N 10240 0.83 of
+    // stream-K's time (1.01), K 20480, N 6144 0.94 (0.98), K 20480, N 4608
+    // 0.95 .. 1.0 (0.96 .. 1.04); K 16384, N 6144 1.04 (1.08)
+    if (MT == 2 && tiles <= 1024 && (K < 16384 || tiles < (K >= 20480 ? 384 : 544))) return;
+    // and only over two or more K ranges, as one leaves up to 112 units
     // idle (K 12288, 24 rows: N 36864 1.16, N 49152 1.15 times as fast with
     // stream-K, weights from HBM)
     if (MT == 2 && S < 2) return;

@@ -112,13 +112,16 @@ def _form(p):
     (60, 7168, 2048, "stream-K"),
     # 0.97, 1.10; 0.99; 1.00, 1.10
     (40, 8192, 4608, "K-split"), (40, 10240, 4608, "stream-K"), (40, 10240, 6144, "K-split"),
-    (24, 14336, 9216, "K-split"), (24, 16384, 9216, "stream-K"),
+    (24, 14336, 9216, "K-split"), (24, 16384, 9216, "wide"),
     # up to 16 rows: 1.02, 1.14; 0.95
     (12, 16384, 9600, "K-split"), (12, 20480, 9600, "stream-K"), (12, 20480, 11264, "K-split"),
     # more than 1024 column tiles: 0.90, 1.27; 0.83, 1.04; 1.18; 0.96, 1.14; 1.08, 0.89
     (4, 7168, 16640, "K-split"), (4, 8192, 16640, "stream-K"), (4, 8192, 28992, "K-split"), (4, 8192, 28800, "stream-K"),
     (4, 8192, 35200, "stream-K"), (24, 4096, 28800, "K-split"), (24, 4096, 32768, "stream-K"),
     (24, 27008, 28800, "stream-K"), (24, 27008, 28992, "K-split"),
+    # wide blocks at 17 to 32 rows: 0.90, 0.92; 0.84; 1.04
+    (32, 28672, 8192, "wide"), (20, 20480, 8192, "wide"), (24, 16384, 8448, "stream-K"), (32, 18432, 8704, "wide"),
+    (32, 18432, 6144, "stream-K"),
     # one K range of wide blocks at 17 to 32 rows 1.15 of stream-K, above 0.9
     (24, 12288, 32768, "wide"), (24, 12288, 36864, "stream-K"), (40, 12288, 49152, "wide")])
 def test_plain_lines_with_weights_from_hbm(plan, M, K, N, form):
