@@ -1311,24 +1311,28 @@ void launch_w4a16_gemm(const GemmLaunch& L, hipStream_t st) {
 }
 
 // The longest K that one-tile K-split workgroups take above 16 rows.  nb: the
-// stream-K form's column blocks.  Above 32 rows it cuts few of them into
-// slivers and is then the slower one on a longer K too (N 1024, 40 rows: nb 8
-// and 0.82 of its time with the K split at K 16384, nb 16 and 1.26 at K 12288).
+// stream-K form's column blocks.  Where nb is a multiple of 8 that form keeps
+// a block's ranges and their fix-up on one XCD and wins from a shorter K on
+// (40 rows, time of the K split over its: N 1024, nb 16, K 8192 1.01, K 10240
+// 1.19; N 1280, nb 20, K 10240 0.85, K 14336 1.10).  Above 32 rows it cuts few
+// blocks into slivers, and from K 16384 on it has half as many, of two tiles
+// per wave (N 1024, nb 8: K 16384 0.81, K 20480 0.87).
 static int ksplit_longest(int MT, int K, int tiles) {
   const int nb = K >= 16384 && tiles % 8 == 0 ? tiles / 8 : tiles / 4;
-  if (MT == 2) return tiles <= 32 ? 20480 : tiles <= 48 ? 16384 : tiles <= 80 ? 10240 : tiles < 224 ? 8192 : 12288;
-  if (nb <= 6) return K;
-  if (nb <= 12) return nb <= 10 ? 20480 : 16384;
-  return tiles <= 80 ? 10240 : tiles < 224 ? 10240 - 1024 * MT : 24576 / MT;
+  if (tiles >= 224) return 24576 / MT;
+  if (K >= 16384) return MT == 2 ? 0 : nb <= 6 ? K : nb <= 10 ? 20480 : nb <= 12 ? 16384 : 0;
+  if (nb % 8 == 0) return (MT > 2 && nb == 8 ? 12288 : 10240) - 1024 * MT;
+  return MT > 2 && nb <= 12 ? 14336 : 10240;
 }
 
 // K-split plan (ksw waves, knt weight tiles per workgroup) of a shape, or
 // ksw = 0 for the stream-K kernel.  The lines come from both forms timed on
-// 3100 shapes (N 256 .. 49152, K 1024 .. 28672, 1 to 60 rows), the weights
-// rotated through more memory than the Infinity Cache holds, as those of a
-// model are; "times as fast" and ratios beside them are of that.  Weights
-// read again from the Infinity Cache favour the K split by a further tenth
-// to a fifth.
+// 5000 shapes (N 256 .. 49152, K 1024 .. 28672, 1 to 62 rows, the plain ones
+// with and without a residual, which favours stream-K by up to a tenth), the
+// weights rotated through more memory than the Infinity Cache holds, as those
+// of a model are; "times as fast" and ratios beside them are of that.  Weights
+// read again from the Infinity Cache favour the K split by a further tenth to
+// a fifth.
 static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& p) {
   const int G = K / 128;
   if (swiglu) {
@@ -1339,11 +1343,17 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
     if (tiles > 1088 && (M > 8 || tiles > 1536 || K > 4096)) return;
     // few column tiles on a long K, as for the plain form below (K 27264, N
     // 1088, 59 rows 56.1 -> 33.0 us with stream-K; K 12288, N 2048 1.05 and
-    // 1.12 times as fast at 40 and 60 rows; K 28672, N 6144 1.10 at 14 rows)
+    // 1.12 times as fast at 40 and 60 rows; K 28672, N 5120 1.10 at 2 and 14
+    // rows, K 20480 1.06 at 16)
     if (tiles < 448) {
-      if (MT >= 3 && tiles > 16 && K > (tiles <= 32 ? 16384 : tiles <= 160 ? 10240 : 12288)) return;
-      if (M > 8 && tiles > 48 && K > 24576) return;
+      if (MT >= 3 && tiles > 16 && K > (tiles <= 32 ? 16384 : 10240)) return;
+      if (K > 20480 && tiles > (M > 8 ? 48 : 256)) return;
     }
+    // more than one workgroup per compute unit in two rounds that are not
+    // full (17 to 32 rows, N 17408: K 6144 1.07, K 12288 1.05; 60 rows, K
+    // 4096, N 9600 1.10)
+    if (MT == 2 && tiles > 1024) return;
+    if (MT == 4 && tiles > 512 && tiles < 832 && K > 3584) return;
     // above 32 rows at more than one workgroup per compute unit only for a
     // short K (K 5888, N 10816, 64 rows: 34.5 against 36.4 us)
     if (tiles > 512 && MT >= 3 && (K > 4096 || tiles > 1024)) return;
@@ -1367,22 +1377,28 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
     p.knt = 1;
   } else if (tiles <= 512) {
     // N 8192, K 28672, 32 rows: 39.4 us with stream-K, 43.5 with the K split
-    // (weights from the Infinity Cache); above 32 rows N 4608, K 10240 1.11
+    // (weights from the Infinity Cache); above 32 rows N 4608, K 10240 1.12
     // times as fast with stream-K
     if (MT > 1 && MT * K > 32768) return;
-    if (MT > 2 && K > 8192 && tiles < 320) return;
+    // fewer columns a shorter K (24 rows, N 4352, K 12288 1.08)
+    if (MT > 1 && tiles < 384 && K > (MT == 2 ? 10240 : 8192)) return;
+    // up to 16 rows K 28672, N 4352 .. 7168 1.05 .. 1.10, K 20480 1.0
+    if (K > 24576) return;
     p.knt = 2;
   } else if (tiles <= 1024) {
     // above 32 rows fewer than 192 workgroups do not pay on a long K (N
     // 11904, K 16896, 45 rows: 40.1 against 44.7 us; N 14144, K 25472: 75.3
     // against 64.8; weights from the Infinity Cache)
-    if (MT >= 3 && K > 8192 && tiles < 768) return;
+    // and fewer than 160 not on a shorter one (N 8448, K 8192 1.10 times as
+    // fast with stream-K, K 6144 0.98)
+    if (MT >= 3 && K > (tiles < 640 ? 6144 : 8192) && tiles < 768) return;
     // nor any number from 17 rows on a longer one (N 9216, K 16384, 24 rows
     // 1.12 times as fast with stream-K; N 12544, K 19456, 22 rows: 45.1
     // against 42.3 us, weights from the Infinity Cache)
     if (MT >= 2 && K > (tiles < 768 ? 14336 : 16384)) return;
-    // nor up to 16 rows (N 9600, K 20480, 12 rows 1.19 times as fast)
-    if (K > 16384 && tiles < 704) return;
+    // nor up to 16 rows (16 rows: N 8448, K 14336 1.07 times as fast; N 12288,
+    // K 20480 1.10; N 14336, K 28672 1.0)
+    if (MT == 1 && K > (tiles < 704 ? 12288 : 16384) && tiles < 896) return;
     p.knt = K <= 2048 && MT <= 2 ? 2 : 4;
   } else {
     // beyond 256 workgroups only where they fill whole rounds of the chip (N
@@ -1392,10 +1408,10 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
     // not where K is a multiple of 8192, so that every tile begins at a
     // multiple of 64 KB (4 rows, K 8192: N 16640 1.29 and N 35200 1.19 times
     // as fast with stream-K; but N 28992, where stream-K has one tile per
-    // wave, 0.85), nor at 17 to 32 rows for a multiple of 4096 and N one of
-    // 8192 (K 4096, N 32768: 1.14)
+    // wave, 0.85), nor from 17 rows on for N a multiple of 32768 (46
+    // rows: K 2048 1.22, K 4096 1.16, K 7168 1.0)
     if (MT == 1 && K % 8192 == 0 && (tiles % 8 == 0 || tiles < 1600)) return;
-    if (MT == 2 && K % 4096 == 0 && tiles % 512 == 0) return;
+    if (MT >= 2 && tiles % 2048 == 0) return;
     // nor from 17 rows on a very long K (K 27008, N 32768, 24 rows: 1.18; N 28992 0.92)
     if (MT >= 2 && K > 16384 && tiles % 8 == 0) return;
     p.knt = K <= 2048 && MT <= 2 ? 2 : 4;

@@ -101,23 +101,27 @@ def _form(p):
 # Both sides of the plan's lines, with the time of the K-split form over that
 # of stream-K, weights from HBM.
 @pytest.mark.parametrize("M,K,N,form", [
-    # few columns, 17 rows and more: 0.77, 1.16; 0.91, 1.10; 0.97, 1.09
-    (24, 8192, 1024, "K-split"), (24, 12288, 1024, "stream-K"), (24, 16384, 768, "K-split"), (24, 20480, 768, "stream-K"),
-    (24, 8192, 1536, "K-split"), (24, 10240, 1536, "stream-K"),
-    # 0.84, 1.04; 0.90, 1.26; 0.82 (fewer stream-K blocks from K 16384); 0.94 at any K
-    (40, 7168, 1536, "K-split"), (40, 8192, 1536, "stream-K"), (40, 10240, 1024, "K-split"), (40, 12288, 1024, "stream-K"),
-    (40, 16384, 1024, "K-split"), (40, 28672, 768, "K-split"),
-    # 0.77, 1.16; 1.46; 0.96, 1.10
-    (60, 6144, 1536, "K-split"), (60, 8192, 1536, "stream-K"), (60, 12288, 1024, "stream-K"), (60, 6144, 2048, "K-split"),
-    (60, 7168, 2048, "stream-K"),
-    # 0.97, 1.10; 0.99; 1.00, 1.10
-    (40, 8192, 4608, "K-split"), (40, 10240, 4608, "stream-K"), (40, 10240, 6144, "K-split"),
+    # few columns, 17 rows and more, stream-K's blocks a multiple of 8: 1.02, 1.09; 0.93, 1.09; 0.91, 1.12
+    (24, 8192, 1024, "K-split"), (24, 9216, 1024, "stream-K"), (46, 7168, 1024, "K-split"), (46, 9216, 1024, "stream-K"),
+    (62, 6144, 1024, "K-split"), (62, 8192, 1024, "stream-K"),
+    # 1.0, 1.08; 1.0, 1.12
+    (24, 8192, 2048, "K-split"), (40, 8192, 1536, "stream-K"), (60, 6144, 2048, "K-split"), (60, 7168, 2048, "stream-K"),
+    # not a multiple: 0.99, 1.11; 0.93, 1.05; 0.98, 1.13; 0.91, 1.04
+    (30, 10240, 768, "K-split"), (30, 12288, 768, "stream-K"), (46, 10240, 1792, "K-split"), (46, 12288, 1792, "stream-K"),
+    (62, 10240, 1792, "K-split"), (62, 12288, 1792, "stream-K"), (62, 10240, 1280, "K-split"), (62, 12288, 1280, "stream-K"),
+    # few blocks: 0.98, 0.81; 0.92, 1.26; 0.94
+    (62, 14336, 768, "K-split"), (40, 16384, 1024, "K-split"), (62, 20480, 1024, "K-split"), (62, 28672, 1024, "stream-K"),
+    (40, 28672, 768, "K-split"),
+    # 0.98, 1.04; 1.02, 1.12; 1.01; 1.02, 1.10
+    (24, 10240, 4608, "K-split"), (24, 12288, 4608, "stream-K"), (40, 8192, 4608, "K-split"), (40, 10240, 4608, "stream-K"),
+    (40, 10240, 6144, "K-split"), (46, 6144, 8448, "K-split"), (46, 8192, 8448, "stream-K"),
+    # up to 16 rows: 0.98, 1.07; 0.95, 1.07; 1.0, 1.10; 0.95
+    (16, 20480, 4608, "K-split"), (16, 28672, 4608, "stream-K"), (16, 12288, 8448, "K-split"), (16, 14336, 8448, "stream-K"),
+    (16, 16384, 12288, "K-split"), (16, 20480, 12288, "stream-K"), (16, 28672, 14336, "K-split"),
     (24, 14336, 9216, "K-split"), (24, 16384, 9216, "wide"),
-    # up to 16 rows: 1.02, 1.14; 0.95
-    (12, 16384, 9600, "K-split"), (12, 20480, 9600, "stream-K"), (12, 20480, 11264, "K-split"),
-    # more than 1024 column tiles: 0.90, 1.27; 0.83, 1.04; 1.18; 0.96, 1.14; 1.08, 0.89
+    # more than 1024 column tiles: 0.90, 1.27; 0.83, 1.04; 1.18; 0.96, 1.16; 1.08, 0.89
     (4, 7168, 16640, "K-split"), (4, 8192, 16640, "stream-K"), (4, 8192, 28992, "K-split"), (4, 8192, 28800, "stream-K"),
-    (4, 8192, 35200, "stream-K"), (24, 4096, 28800, "K-split"), (24, 4096, 32768, "stream-K"),
+    (4, 8192, 35200, "stream-K"), (24, 4096, 28800, "K-split"), (46, 4096, 32768, "stream-K"),
     (24, 27008, 28800, "stream-K"), (24, 27008, 28992, "K-split"),
     # wide blocks at 17 to 32 rows: 0.90, 0.92; 0.84; 1.04
     (32, 28672, 8192, "wide"), (20, 20480, 8192, "wide"), (24, 16384, 8448, "stream-K"), (32, 18432, 8704, "wide"),
@@ -129,13 +133,14 @@ def test_plain_lines_with_weights_from_hbm(plan, M, K, N, form):
 
 
 @pytest.mark.parametrize("M,K,N,form", [
-    # up to 8 rows any K; above: 0.98, 1.10; 1.08 at 24 rows
-    (8, 28672, 6144, "K-split"), (14, 20480, 6144, "K-split"), (14, 28672, 6144, "stream-K"),
+    # up to 32 rows: 1.0, 1.10 (also at 2 rows); 0.98
+    (14, 20480, 6144, "K-split"), (14, 28672, 6144, "stream-K"), (2, 28672, 5120, "stream-K"), (8, 28672, 4096, "K-split"),
     (24, 20480, 1024, "K-split"), (24, 28672, 1024, "stream-K"),
-    # above 32 rows: 0.95, 1.05; 1.12 at 60; 0.91, 1.01 .. 1.13; 0.98, 1.10; up to 256 columns any K: 0.80
+    # above 32 rows: 0.95, 1.05; 1.12 at 60; 0.94, 1.13; up to 256 columns any K: 0.80; many columns too: 0.95
     (40, 10240, 2048, "K-split"), (40, 12288, 2048, "stream-K"), (60, 12288, 2048, "stream-K"),
-    (40, 16384, 512, "K-split"), (60, 20480, 512, "stream-K"), (40, 12288, 5120, "K-split"), (60, 16384, 5120, "stream-K"),
-    (40, 28672, 256, "K-split"), (40, 28672, 7168, "K-split"),
+    (40, 16384, 512, "K-split"), (60, 20480, 512, "stream-K"), (40, 28672, 256, "K-split"), (40, 28672, 7168, "K-split"),
+    # two rounds of workgroups: 0.91, 1.07; 0.87, 1.10
+    (24, 6144, 16384, "K-split"), (24, 6144, 17408, "stream-K"), (60, 3584, 9600, "K-split"), (60, 4096, 9600, "stream-K"),
     # more than 1088 column tiles, up to 8 rows: 0.80, 0.82; 0.89; 1.0
     (1, 3072, 17664, "K-split"), (8, 4096, 19200, "K-split"), (8, 1536, 24576, "K-split"), (8, 2048, 28672, "stream-K"),
     (8, 4224, 17664, "stream-K"), (9, 3072, 17664, "stream-K")])
