@@ -177,7 +177,8 @@ int swiftspec_rmsnorm(const uint16_t* x, int32_t M, int32_t H, int32_t ldx, cons
  * with xn[m] = x[m] / sqrt(mean_k x[m][k]^2 + eps) * gamma over the K
  * columns, xn rounded to fp16 (as swiftspec_rmsnorm computes it) and then
  * multiplied.  Where the GEMM's plan gives each workgroup all of K and K is
- * short enough for its registers (up to 16 rows, 1024 <= K <= 2048)
+ * short enough for its registers (up to 16 rows, 1024 <= K <= 2048; up to 8
+ * rows and N <= 4096 also K <= 4096, not the SwiGLU)
  * the norm runs inside the GEMM, which sums the rows' squares first and
  * forms the fp16 operand values the same way; otherwise, and where y
  * overlaps x, the norm kernel writes them for the GEMM.  x [M][ldx],

@@ -1285,6 +1285,8 @@ void launch_w4a16_gemm(const GemmLaunch& L, hipStream_t st) {
       if (L.ksw == 8) launch_ksn<8, 4, true>(L, st);
       else if (L.K <= 1024) L.knt == 2 ? launch_ksn<4, 2, true>(L, st) : launch_ksn<4, 4, true>(L, st);
       else L.knt == 2 ? launch_ksn<4, 2, true, 4>(L, st) : launch_ksn<4, 4, true, 4>(L, st);
+    } else if (L.K > 2048) {
+      launch_ksn<8, 1, false, 4>(L, st);
     } else if (L.ksw == 8) {
       L.knt == 1 ? launch_ksn<8, 1, false>(L, st) : L.knt == 2 ? launch_ksn<8, 2, false>(L, st) : launch_ksn<8, 4, false>(L, st);
     } else {
@@ -1474,8 +1476,9 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
 // The RMSNorm runs inside a K-split GEMM where a workgroup holds all of K in
 // registers (1024 <= K <= 2048, one M-tile): every workgroup normalises all
 // of K for itself, so it pays while that is short (K 2048, N 3072, 8 rows:
-// 5.4 us against 6.6 with the norm kernel; at K 3072 and 4096 within 0.3 us
-// of it either way, and slower at N >= 10240).  A SwiGLU has four waves of up
+// 5.4 us against 6.6 with the norm kernel), and up to K 4096 for few rows and
+// a column of one tile (K 3584, N 3712, 2 rows 7.6 against 8.3; 13 rows within
+// 0.05 of it, N >= 10240 slower).  A SwiGLU has four waves of up
 // to four groups where a workgroup's column is one tile or K at most 1536
 // (8 rows, weights from HBM: K 1280, N 2048 1.09 times as fast as eight waves
 // of two groups, N 8192 1.07; K 2048, N 8192 0.97), and one tile up to one
@@ -1483,7 +1486,8 @@ static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
 // empty (N 10240: K 1280 1.17, K 2048 1.04 times as fast).
 bool norm_in_ksplit(GemmPlan& p, int M, int K, int N, bool swiglu) {
   const int G = K / 128, tiles = N / 16;
-  if (!p.ksw || M > 16 || G < 8 || G > 16) return false;
+  const int longest = !swiglu && tiles <= 256 && M <= 8 ? 32 : 16;
+  if (!p.ksw || M > 16 || G < 8 || G > longest) return false;
   if (swiglu) {
     p.knt = tiles <= 256 || (tiles > 512 && tiles <= 832) ? 2 : 4;
     p.ksw = p.knt == 2 || G <= 12 ? 4 : 8;

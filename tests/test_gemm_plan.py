@@ -159,3 +159,12 @@ def test_swiglu_with_norm_has_four_waves(plan, norm, K, N, waves, tiles):
     for M in (1, 8, 16):
         p = plan(M, K, N, True)
         assert norm(p, M, K, N, True) and (p.ksw, p.knt) == (waves, tiles)
+
+
+def test_norm_in_the_gemm_up_to_k_4096_for_few_rows(plan, norm):
+    """Up to 8 rows and 256 column tiles the norm stays inside the GEMM up to
+    K 4096 (K 3584, N 3712, 2 rows: the norm kernel 1.10 of its time)."""
+    for M, K, N, inside in ((8, 4096, 4096, True), (1, 3584, 3712, True), (9, 2176, 4096, False), (8, 2176, 4160, False),
+                            (8, 4224, 4096, False), (9, 2048, 4096, True)):
+        assert norm(plan(M, K, N, False), M, K, N, False) == inside, (M, K, N)
+    assert not norm(plan(8, 2176, 4096, True), 8, 2176, 4096, True)

@@ -432,6 +432,8 @@ def test_w4a16_stream_k_forms(M, K, N, swiglu):
     (17, 2048, 3072, 2048, False), (32, 8192, 1024, 8200, False),  # norm kernel, then stream-K
     (4, 1024, 2048, 1024, True), (8, 2048, 8192, 2048, True), (3, 1920, 4096, 2056, True),  # in the SwiGLU
     (9, 2048, 8192, 2048, True),                                  # norm kernel, then the SwiGLU
+    # in the GEMM, eight waves of three and four groups
+    (8, 2944, 4096, 2944, False), (3, 4096, 2048, 4104, False), (1, 2176, 512, 2176, False),
     # in the SwiGLU, four waves of up to four groups (three at K 1408): one column tile per workgroup, two
     (5, 2048, 10240, 2048, True), (16, 1408, 3072, 1416, True), (8, 1408, 6144, 1408, True), (13, 1536, 8192, 1536, True)])
 def test_rmsnorm_then_projection_matches_oracle(M, K, N, ldx, swiglu):
