@@ -104,12 +104,13 @@ bool rows_overlap(const uint16_t* a, int lda, int na, const uint16_t* b, int ldb
   return false;
 }
 
-// The norm runs inside the GEMM where the plan allows it, unless y overlaps
-// x: each of the GEMM's workgroups reads all of x, with no order between one
-// workgroup's reads and another's stores to y.
+// The norm runs inside the GEMM where the plan allows it, unless 16 rows of x
+// reach 4 GiB (the GEMM addresses the rows of its M-tile by 32-bit offsets)
+// or y overlaps x: each of the GEMM's workgroups reads all of x, with no order
+// between one workgroup's reads and another's stores to y.
 bool norm_in_gemm(const swiftspec_w4* W0, bool swiglu, const NormIn& n, int M, const uint16_t* y, int ldy) {
   ss::GemmPlan p = ss::plan_w4a16_gemm(M, W0->K, W0->N, swiglu);
-  return ss::norm_in_ksplit(p, M, W0->K, W0->N, swiglu) &&
+  return ss::norm_in_ksplit(p, M, W0->K, W0->N, swiglu) && (uint64_t)n.ldx * 32 <= 0xFFFFFFFFull &&
          !rows_overlap(n.x, n.ldx, W0->K, y, ldy, W0->N, M);
 }
 

@@ -996,7 +996,7 @@ __global__ __launch_bounds__(64 * W) void w4a16_ksplit_norm_kernel(GemmArgs a) {
   const auto rgm = buffer_rsrc(a.gamma + g0 * 128, (uint32_t)(n * 256));
   const uint32_t lane16 = (uint32_t)lane * 16u, col4 = (uint32_t)ncol * 4u;
   // this lane's 32 values k = 128 g + 32 kq + t of row ncol, at g = 0
-  const uint32_t xrow = (uint32_t)((ncol * a.ldx + 32 * kq) * 2);
+  const uint32_t xrow = ((uint32_t)ncol * (uint32_t)a.ldx + 32u * (uint32_t)kq) * 2u;
   const int xsw = ncol & 3;  // load f takes chunk f ^ xsw
   const uint32_t xm1 = 0u - (uint32_t)(xsw & 1), xm2 = 0u - (uint32_t)(xsw >> 1);
 

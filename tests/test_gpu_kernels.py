@@ -531,6 +531,30 @@ def test_rmsnorm_projection_in_place(M, K, N, ldx, swiglu):
     assert np.array_equal(down16(wide[:, :ldx]), x)
 
 
+@pytest.mark.parametrize("ldx", [(1 << 27) - 8, 1 << 27])
+def test_rmsnorm_projection_rows_far_apart(ldx):
+    """16 rows just under and over 4 GiB: the same result as with rows side
+    by side (from 2^27 elements apart that of the norm kernel followed by the
+    GEMM, which sums the squares in another order)."""
+    M, K, N = 16, 1024, 1024
+    W = _rand_w4(95, N, K)
+    t, d = upload_w4(W)
+    x, dg = up(gen.normal_f16(95, 1, (M, K), 0.0, 2.0)), up(gen.normal_f16(95, 2, (K,), 1.0, 0.2))
+    ws = ss.workspace(ss.gemm_workspace_bytes(M, K, N), dev())
+    far = torch.empty((M - 1) * ldx + K, dtype=torch.int16, device=dev()).as_strided((M, K), (ldx, 1))
+    far.copy_(x)
+    outs = [torch.zeros((M, N), dtype=torch.int16, device=dev()) for _ in range(2)]
+    ss.rmsnorm_w4a16_gemm(d, far, dg, outs[0], ws)
+    if ldx < 1 << 27:
+        ss.rmsnorm_w4a16_gemm(d, x, dg, outs[1], ws)
+    else:
+        xn = torch.zeros((M, K), dtype=torch.int16, device=dev())
+        ss.rmsnorm(x, dg, xn)
+        ss.w4a16_gemm(d, xn, outs[1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("M,K,N", [(1, 1024, 1024), (8, 2048, 512), (13, 1024, 2048), (32, 8192, 1024),
                                    (40, 4096, 1024), (64, 2048, 1024)])
 def test_w4a16_gemm_valu_variant_matches_oracle(M, K, N):
