@@ -47,7 +47,9 @@ __device__ __forceinline__ void lm_wait(int behind) {
   }
 }
 
-template <int MT, int kLmCols, int NS>
+// kLong: rows of 64 MiB and more, 64 of which pass what a 32-bit buffer offset
+// reaches: 64-bit addresses (rows past V or M repeat the last one).
+template <int MT, int kLmCols, int NS, bool kLong>
 __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(LmArgs a) {
   constexpr int kWBytes = kLmCols * 2048;                    // weights of a stage, per wave
   constexpr int kXBytes = MT * 2048;                         // activations of a stage
@@ -86,10 +88,28 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(LmArgs a) {
   }
   // the stage this workgroup begins at (multiplicative hash)
   const int rot = __builtin_amdgcn_readfirstlane((int)(((blockIdx.x * 2654435761u) >> 16) % (unsigned)nst));
+  // LDS byte `at` of the ring from rows 8 l .. 8 l + 7 of m (n rows), k's from 64 k on
+  auto load_long = [&](const uint16_t* m, int n, int l, int k, uint32_t at) {
+    const int row = 8 * l + lr;
+    const uint16_t* src = m + (size_t)min(row, n - 1) * a.H + (size_t)k * kLmK + (lp ^ ((row >> 1) & 7)) * 8;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)(smem + at), 16, 0, 0);
+  };
   auto issue = [&](int t) {
-    const uint32_t st = lds0 + (uint32_t)((t % NS) * kStage);
+    const uint32_t slot = (uint32_t)((t % NS) * kStage), st = lds0 + slot;
     const int k = t + rot < nst ? t + rot : t + rot - nst;  // 64 k's from 64 k on
     const uint32_t off = (uint32_t)k * (kLmK * 2);
+    if constexpr (kLong) {
+#pragma unroll
+      for (int l = 0; l < kLmCols * 2; ++l)
+        load_long(a.W + (size_t)first * a.H, min(kLmCols * 16, a.V - first), l, k, slot + kXBytes + wave * kWBytes + l * 1024);
+#pragma unroll
+      for (int j = 0; j < kXLoads; ++j) {
+        const int l = (wave + kLmWaves * j) % (MT * 2);
+        load_long(a.xn, a.M, l, k, slot + l * 1024);
+      }
+      return;
+    }
 #pragma unroll
     for (int l = 0; l < kLmCols * 2; ++l) buffer_load_lds16(rw, wv[l], off, st + kXBytes + wave * kWBytes + l * 1024);
 #pragma unroll
@@ -153,15 +173,15 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(LmArgs a) {
 
 // kLmCols tiles per wave; NS stages: two workgroups per compute unit with one
 // or two tiles, one with four (136 to 144 KB of LDS)
-template <int C>
+template <int C, bool kLong = false>
 static void launch_cols(const LmArgs& a, hipStream_t st) {
   constexpr int kSmall = C == 1 ? 6 : 4, kLarge = C == 1 ? 4 : 3;
   const dim3 grid((a.V / 16 + kLmWaves * C - 1) / (kLmWaves * C)), wg(64 * kLmWaves);
   switch ((a.M + 15) / 16) {
-    case 1: hipLaunchKernelGGL((lm_head_kernel<1, C, kSmall>), grid, wg, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((lm_head_kernel<2, C, kSmall>), grid, wg, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((lm_head_kernel<3, C, kLarge>), grid, wg, 0, st, a); break;
-    default: hipLaunchKernelGGL((lm_head_kernel<4, C, kLarge>), grid, wg, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((lm_head_kernel<1, C, kSmall, kLong>), grid, wg, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((lm_head_kernel<2, C, kSmall, kLong>), grid, wg, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((lm_head_kernel<3, C, kLarge, kLong>), grid, wg, 0, st, a); break;
+    default: hipLaunchKernelGGL((lm_head_kernel<4, C, kLarge, kLong>), grid, wg, 0, st, a); break;
   }
 }
 
@@ -172,7 +192,8 @@ void launch_lm_head(const uint16_t* xn, int M, int H, const uint16_t* W, int V, 
   // (V 128256, 64 rows: 366 against 381 us with 128), 64 where 128 would leave
   // half of the units idle (V 8704: 30 against 41 us)
   const int n4 = (V + 255) / 256, rounds = (n4 + 255) / 256;
-  if (V > 65536 && 10 * n4 >= 9 * 256 * rounds) launch_cols<4>(a, st);
+  if (H >= 1 << 25) launch_cols<1, true>(a, st);
+  else if (V > 65536 && 10 * n4 >= 9 * 256 * rounds) launch_cols<4>(a, st);
   else if (V > 16384) launch_cols<2>(a, st);
   else launch_cols<1>(a, st);
 }

@@ -88,3 +88,27 @@ def test_lm_head_rejects_bad_arguments():
         ss.lm_head(h, g, W, out, ws)  # V % 16 != 0
     with pytest.raises(RuntimeError):
         ss.lm_head(h, g, W[:16], out, ss.workspace(16, dev()))  # workspace too small
+
+
+@pytest.mark.parametrize("M,H,V", [(64, 1 << 25, 32), (17, (1 << 26) + 128, 48)])
+def test_lm_head_long_rows(M, H, V):
+    """Rows of 64 MiB and more (64 rows reach 4 GiB): against float64 on the
+    GPU, with hidden states that are zero but for 4096 columns spread over
+    the rows (the norm's sum of squares and the products see those alone)."""
+    g = torch.Generator(device=dev())
+    g.manual_seed(H + M)
+    cols = torch.arange(4096, device=dev()) * (H // 4096) + torch.randint(0, H // 4096, (4096,), generator=g, device=dev())
+    h = torch.zeros((M, H), dtype=torch.float16, device=dev())
+    hc = torch.randn((M, 4096), generator=g, device=dev()).half()
+    h[:, cols] = hc
+    gamma = torch.ones(H, dtype=torch.float16, device=dev())
+    W = torch.empty((V, H), dtype=torch.float16, device=dev()).normal_(0.0, 0.02 * (4096.0 / H) ** 0.5, generator=g)
+    out = torch.zeros((M, V), dtype=torch.float16, device=dev())
+    ws = ss.workspace(ss.lm_head_workspace_bytes(M, H, V), dev())
+    ss.lm_head(h, gamma, W, out, ws)
+    torch.cuda.synchronize()
+    x = hc.double()
+    xn = (x / (x.pow(2).sum(1, keepdim=True) / H + 1e-5).sqrt()).half().double()
+    ref = xn @ W[:, cols].double().T
+    check_close(down16(out.view(torch.int16)), ref.cpu().numpy().astype(np.float16).view(np.uint16),
+                f"lm_head M={M} H={H} V={V}")
