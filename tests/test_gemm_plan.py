@@ -1,9 +1,12 @@
-"""CPU checks of the W4A16 GEMM plans: workspace sizes, and the form that each
-shape of the GPU tests takes."""
+"""CPU checks of the W4A16 GEMM plans: workspace sizes, both sides of the plan's
+lines, and the kernel instance that each shape of the GPU tests runs."""
 import ctypes
 import os
+import sys
 
 import pytest
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 
 
 class Plan(ctypes.Structure):
@@ -168,3 +171,62 @@ def test_norm_in_the_gemm_up_to_k_4096_for_few_rows(plan, norm):
                             (8, 4224, 4096, False), (9, 2048, 4096, True)):
         assert norm(plan(M, K, N, False), M, K, N, False) == inside, (M, K, N)
     assert not norm(plan(8, 2176, 4096, True), 8, 2176, 4096, True)
+
+
+def _instance(p, M, K, N, swiglu):
+    """The kernel instance of plan p, and whether its blocks are split."""
+    mt = (M + 15) // 16
+    if p.wide:
+        return "wide", mt, swiglu, p.nwg > p.nblocks
+    if p.ksw:
+        return "K-split", p.ksw, mt, p.knt, swiglu
+    return "stream-K", mt, p.nw, swiglu, p.nblocks % p.nwg != 0
+
+
+def _norm_instance(p, K, swiglu):
+    groups = (4 if p.ksw == 4 and K > 1024 else 2) if swiglu else (4 if K > 2048 else 2)
+    assert (K // 128 + p.ksw - 1) // p.ksw <= groups
+    return "norm", p.ksw, p.knt, swiglu, groups
+
+
+def _cases(test):
+    """The shapes of a parametrised GPU test."""
+    return [tuple(c) for m in test.pytestmark if m.name == "parametrize" for c in m.args[1]]
+
+
+@pytest.fixture(scope="module")
+def gpu_tests():
+    import test_gpu_kernels
+    return test_gpu_kernels
+
+
+def test_gpu_tests_run_the_forms_they_name(plan, norm, gpu_tests):
+    for test, form in ((gpu_tests.test_w4a16_k_split_forms, "K-split"), (gpu_tests.test_w4a16_wide_blocks, "wide"),
+                       (gpu_tests.test_w4a16_stream_k_forms, "stream-K")):
+        for c in _cases(test):
+            assert _form(plan(*c)) == form, c
+    split = [_instance(plan(*c), *c) for c in _cases(gpu_tests.test_w4a16_split_blocks_reuse_one_workspace)]
+    assert all(i[-1] is True for i in split[3:]) and {i[0] for i in split} == {"K-split", "stream-K", "wide"}
+    inside = [norm(plan(M, K, N, sw), M, K, N, sw)
+              for M, K, N, ldx, sw in _cases(gpu_tests.test_rmsnorm_then_projection_matches_oracle)]
+    assert inside == [True] * 15 + [False] * 8 + [True] * 7
+
+
+def test_every_instance_the_plan_reaches_runs_in_a_gpu_test(plan, norm, gpu_tests):
+    reached, tested = set(), set()
+    for swiglu in (False, True):
+        for K in KS + (1024, 1152, 1408, 1920, 2048, 2176, 16512, 20864):
+            for N in NS + (1024, 4160, 6144, 8256, 16384, 17472):
+                for M in ROWS:
+                    p = plan(M, K, N, swiglu)
+                    reached.add(_instance(p, M, K, N, swiglu))
+                    if norm(p, M, K, N, swiglu):
+                        reached.add(_norm_instance(p, K, swiglu))
+    for test in (gpu_tests.test_w4a16_k_split_forms, gpu_tests.test_w4a16_wide_blocks, gpu_tests.test_w4a16_stream_k_forms):
+        tested |= {_instance(plan(*c), *c) for c in _cases(test)}
+    for M, K, N, ldx, swiglu in _cases(gpu_tests.test_rmsnorm_then_projection_matches_oracle):
+        p = plan(M, K, N, swiglu)
+        if norm(p, M, K, N, swiglu):
+            tested.add(_norm_instance(p, K, swiglu))
+    assert reached <= tested, sorted(map(str, reached - tested))
+    assert len(reached) > 50

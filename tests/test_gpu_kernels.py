@@ -218,10 +218,9 @@ def test_w4a16_gemm_small_shapes_ragged_M(M):
 @pytest.mark.parametrize("M,K,N", [(1, 1024, 2048), (5, 1920, 2048), (8, 2048, 3072), (13, 8192, 2048),
                                    (16, 4096, 4096), (16, 1152, 4096)])
 def test_w4a16_gemm_k_split_workgroups(M, K, N):
-    """Up to 16 rows and at most 32 MB of weights (the 8B down projection,
-    29 MB, runs in the config-shape test): one workgroup per column tile, 4
-    (K < 2048) or 8 waves splitting K into unequal group ranges where G is
-    not a multiple of the wave count (K = 1152, 1920), partials added in wave
+    """Up to 16 rows and 256 column tiles: one workgroup per column tile, 8 or
+    (K >= 4096) 16 waves splitting K into unequal group ranges where G is not
+    a multiple of the wave count (K = 1152, 1920), partial sums added in wave
     order; with and without residual, ragged M."""
     _gemm_case(M, K, N, seed=M * 7 + K, residual=(M % 2 == 1))
 
@@ -235,8 +234,8 @@ def test_w4a16_gemm_config_shapes(name):
         _gemm_case(M, K, N, seed=1000 + K + N, residual=True)
 
 
-def test_w4a16_gemm_deterministic_and_split_consistent():
-    K, N, M = 8192, 1024, 32
+@pytest.mark.parametrize("M,K,N", [(32, 8192, 1024), (17, 12800, 2048)])  # K-split workgroups, split stream-K blocks
+def test_w4a16_gemm_deterministic_and_split_consistent(M, K, N):
     W = _rand_w4(9, N, K)
     x = gen.normal_f16(9, 1, (M, K))
     t, d = upload_w4(W)
@@ -252,11 +251,19 @@ def test_w4a16_gemm_deterministic_and_split_consistent():
     check_close(outs[0], oracle.w4a16_gemm(W, x), "gemm det")
 
 
-@pytest.mark.parametrize("M,K,N,swiglu", [(32, 8192, 10240, False), (13, 2048, 4096, False), (64, 4096, 14336, True)])
+@pytest.mark.parametrize("M,K,N,swiglu", [
+    # K-split workgroups (no partials)
+    (32, 8192, 10240, False), (13, 2048, 4096, False), (64, 4096, 14336, True),
+    # stream-K, blocks split: plain with one and two tiles per wave, SwiGLU with 1 to 4 M-tiles
+    (17, 12800, 2048, False), (40, 16512, 2048, False), (9, 20864, 832, True), (17, 20864, 832, True),
+    (40, 4224, 10240, True), (64, 5760, 10240, True),
+    # wide blocks over several K ranges
+    (64, 16896, 6208, False), (64, 7168, 10112, True)])
 def test_w4a16_split_blocks_reuse_one_workspace(M, K, N, swiglu):
-    """Column blocks split between workgroups (partials summed in workgroup
-    order): five calls on one workspace give bit-identical results within
-    tolerance of the oracle and leave the workspace header zero."""
+    """Column blocks whose partial sums several workgroups write (summed in
+    workgroup or range order by the fix-up kernel), and K-split workgroups,
+    which write none: five calls on one workspace give bit-identical results
+    within tolerance of the oracle and leave the workspace header zero."""
     W = _rand_w4(17, N, K)
     t, d = upload_w4(W)
     x = gen.normal_f16(17, 1, (M, K))
@@ -354,35 +361,36 @@ def _swiglu_sampled_case(M, K, N, seed):
 @pytest.mark.parametrize("M,K,N", [(1, 4096, 14336), (8, 2048, 8192), (5, 8192, 7168), (8, 1152, 2048),
                                    (3, 1920, 4096)])
 def test_w4a16_swiglu_k_split_workgroups(M, K, N):
-    """Fused SwiGLU at up to 8 rows and at most 32 MB per matrix (the 1B FFN,
-    the 8B FFN at one row, one GPU's share of the 70B FFN under 4-way tensor
-    parallelism): one workgroup per column tile reads its gate and up tiles,
-    4 waves split K (unequal group ranges at K = 1152 and 1920)."""
+    """Fused SwiGLU at up to 8 rows (the 1B FFN, the 8B FFN at one row, one
+    GPU's share of the 70B FFN under 4-way tensor parallelism): one workgroup
+    reads the gate and up tiles of one or two column tiles, 8 waves split K
+    (unequal group ranges at K = 1152 and 1920)."""
     _swiglu_sampled_case(M, K, N, seed=41 + M)
 
 
 @pytest.mark.parametrize("M,K,N", [(16, 4096, 14336), (9, 4096, 14336), (17, 4096, 14336), (32, 4096, 14336),
                                    (9, 2048, 8192), (31, 2048, 8192)])
 def test_w4a16_swiglu_two_column_blocks(M, K, N):
-    """SwiGLU at the 8B and 1B FFN widths above 8 rows, where the gate and
-    up tiles of a column run in different waves of one workgroup: sampled
-    columns (the first and last 64, 256 random ones) against the oracle, and
-    two calls agree bit for bit."""
+    """SwiGLU at the 8B and 1B FFN widths above 8 rows, K-split workgroups of
+    two column tiles (4 waves at the 8B width) and, for a short K at up to 16
+    rows, of one: sampled columns (the first and last 64, 256 random ones)
+    against the oracle, and two calls agree bit for bit."""
     _swiglu_sampled_case(M, K, N, seed=31 + M)
 
 
 @pytest.mark.parametrize("M,K,N,swiglu", [
-    # one weight tile per workgroup: fewer groups than waves, uneven ranges, 1 to 4 M-tiles, both sides of 24576 = MT K
-    (1, 128, 64, False), (17, 384, 128, False), (48, 1152, 192, False), (64, 6144, 2048, False), (64, 6272, 2048, False),
+    # one weight tile per workgroup: fewer groups than waves, uneven ranges, 16 waves, 1 to 4 M-tiles
+    (1, 128, 64, False), (17, 384, 128, False), (48, 1152, 192, False), (13, 4224, 192, False), (64, 6144, 2048, False),
     # two: 16 waves (one M-tile, K >= 4096) and 8
-    (16, 4224, 4160, False), (33, 2048, 8192, False), (64, 8192, 8192, False),
+    (7, 2176, 4160, False), (16, 4224, 4160, False), (33, 2048, 8192, False), (64, 8192, 8192, False),
     # four: 513 and more column tiles, with 8 waves; two for a short K
-    (7, 2176, 8256, False), (49, 2176, 8256, False), (32, 1024, 8256, False),
+    (7, 2176, 8256, False), (24, 2304, 8256, False), (40, 2048, 14336, False), (49, 2176, 8256, False), (32, 1024, 8256, False),
     # SwiGLU: gate and up of one column tile; of two, with 8 and with 4 waves
-    (16, 256, 448, True), (64, 1408, 1088, True), (31, 2688, 4160, True), (64, 2688, 4160, True),
-    (9, 2688, 8256, True), (48, 2688, 8256, True), (64, 4096, 8256, True),
+    (16, 256, 448, True), (32, 2048, 4096, True), (40, 1408, 1088, True), (64, 1408, 1088, True),
+    (9, 2688, 4160, True), (31, 2688, 4160, True), (40, 2688, 4160, True), (64, 2688, 4160, True),
+    (9, 2688, 8256, True), (17, 2688, 8256, True), (48, 2688, 8256, True),
     # more than 1088 column tiles at up to 8 rows
-    (8, 2944, 20928, True), (1, 1152, 24576, True)])
+    (8, 2944, 20928, True), (1, 1152, 24576, True), (8, 1152, 17472, True)])
 def test_w4a16_k_split_forms(M, K, N, swiglu):
     """The K-split workgroups at the edges of their plan: waves without a
     group, uneven group ranges, every number of M-tiles and of weight tiles
@@ -398,8 +406,9 @@ def test_w4a16_k_split_forms(M, K, N, swiglu):
     (17, 8192, 18432, True), (48, 512, 18432, True), (64, 1536, 18496, True), (33, 1024, 32768, True),
     # two and three (ranges of unequal length), above 32 rows only
     (48, 4608, 13568, True), (64, 7168, 10112, True),
-    # plain: 2, 3 and 9 ranges, a block cut off by the last column
-    (32, 8192, 32768, False), (45, 8192, 21184, False), (64, 16896, 6208, False)])
+    # plain: 2, 3 and 9 ranges and one, a block cut off by the last column
+    (32, 8192, 32768, False), (45, 8192, 21184, False), (64, 16896, 6208, False), (48, 8192, 36736, False),
+    (64, 8192, 36736, False)])
 def test_w4a16_wide_blocks(M, K, N, swiglu):
     """The wide blocks at the edges of their plan, against the oracle."""
     if swiglu:
@@ -412,8 +421,10 @@ def test_w4a16_wide_blocks(M, K, N, swiglu):
     # plain, one and two tiles per wave, 1 to 4 M-tiles, split blocks
     (8, 8320, 17472, False), (8, 8320, 17408, False), (17, 12800, 2048, False), (17, 16512, 2048, False),
     (40, 8320, 2048, False), (40, 16512, 2048, False), (64, 8320, 2048, False), (64, 16512, 2048, False),
-    # SwiGLU: a K that is no multiple of the wide blocks' step
-    (8, 1152, 17472, True), (32, 1152, 17472, True), (47, 1152, 17472, True), (64, 1152, 17472, True)])
+    (64, 6272, 2048, False),
+    # SwiGLU: whole blocks, a K that is no multiple of the wide blocks' step; split blocks
+    (16, 1152, 17472, True), (32, 1152, 17472, True), (47, 1152, 17472, True), (64, 1152, 17472, True),
+    (9, 20864, 832, True), (17, 20864, 832, True), (40, 4224, 10240, True), (64, 4096, 8256, True)])
 def test_w4a16_stream_k_forms(M, K, N, swiglu):
     """The stream-K form at the shapes that neither other form takes."""
     if swiglu:
@@ -423,27 +434,31 @@ def test_w4a16_stream_k_forms(M, K, N, swiglu):
 
 
 @pytest.mark.parametrize("M,K,N,ldx,swiglu", [
-    # norm inside the K-split GEMM: 2 groups per wave, then up to 4
+    # norm inside the K-split GEMM (up to 16 rows): 8 waves of one or two groups, 4 waves of two; one, two and
+    # four column tiles per workgroup
     (8, 2048, 3072, 2048, False), (1, 2048, 3072, 2048, False), (6, 1024, 2048, 1032, False),
-    (8, 1152, 2048, 1280, False), (5, 1920, 2048, 1920, False), (13, 4096, 6144, 4096, False),
-    (16, 1152, 2048, 1288, False), (16, 4096, 4096, 4096, False),
-    # norm kernel, then the K-split GEMM (8 and 16 groups per wave)
-    (7, 8192, 2560, 8192, False), (3, 16384, 2048, 16384, False),
-    (17, 2048, 3072, 2048, False), (32, 8192, 1024, 8200, False),  # norm kernel, then stream-K
-    (4, 1024, 2048, 1024, True), (8, 2048, 8192, 2048, True), (3, 1920, 4096, 2056, True),  # in the SwiGLU
-    (9, 2048, 8192, 2048, True),                                  # norm kernel, then the SwiGLU
+    (8, 1152, 2048, 1280, False), (5, 1920, 2048, 1920, False), (16, 1152, 2048, 1288, False),
+    (8, 2048, 6144, 2048, False), (8, 2048, 16384, 2048, False), (8, 1024, 6144, 1024, False), (8, 1024, 16384, 1024, False),
+    # in the SwiGLU, 4 waves of two groups and 8 of up to two; one and two column tiles
+    (4, 1024, 2048, 1024, True), (8, 1024, 8192, 1024, True), (8, 2048, 8192, 2048, True), (9, 2048, 8192, 2048, True),
+    (3, 1920, 4096, 2056, True),
+    # norm kernel, then the K-split GEMM
+    (13, 4096, 6144, 4096, False), (16, 4096, 4096, 4096, False), (7, 8192, 2560, 8192, False),
+    (3, 16384, 2048, 16384, False), (17, 2048, 3072, 2048, False), (32, 8192, 1024, 8200, False),
+    # norm kernel, then stream-K; then the SwiGLU
+    (24, 12800, 2048, 12800, False), (9, 2176, 4096, 2176, True),
     # in the GEMM, eight waves of three and four groups
     (8, 2944, 4096, 2944, False), (3, 4096, 2048, 4104, False), (1, 2176, 512, 2176, False),
     # in the SwiGLU, four waves of up to four groups (three at K 1408): one column tile per workgroup, two
     (5, 2048, 10240, 2048, True), (16, 1408, 3072, 1416, True), (8, 1408, 6144, 1408, True), (13, 1536, 8192, 1536, True)])
 def test_rmsnorm_then_projection_matches_oracle(M, K, N, ldx, swiglu):
     """RMSNorm followed by the QKV-style projection or the fused SwiGLU,
-    against the reference's fp16 rmsnorm then its fp64 product: where each
-    workgroup holds all of K and each wave at most 4 groups the norm runs
-    inside the GEMM (row sums first, then the operand normalised as the
-    norm kernel does it; each row's 16-byte chunks loaded in a
+    against the reference's fp16 rmsnorm then its fp64 product: up to 16 rows
+    and for 1024 <= K <= 2048 (up to 8 rows and 256 column tiles 4096) the
+    norm runs inside the GEMM (row sums first, then the operand normalised as
+    the norm kernel does it; each row's 16-byte chunks loaded in a
     row-dependent order), else as its own kernel; both within the GEMM
-    tolerance, with strided rows (ldx > K, also not a multiple of 16 bytes
+    tolerance, with strided rows (ldx > K, also not a multiple of 128 bytes
     apart), ragged M and unequal K ranges per wave (K = 1152, 1920); two
     calls agree bit for bit."""
     seed = 50 + M + K % 1000

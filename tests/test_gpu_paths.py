@@ -134,7 +134,7 @@ def test_swiglu_accepts_the_whole_fp16_range(M, K, N):
 def test_down_projection_70b_with_spiked_input(M):
     """The 70B down projection (K = 28672, N = 8192, + residual) fed an FFN
     activation with large entries; M = 64 is the 80-layer step's instance
-    (four 16-row tiles, two column tiles per wave)."""
+    (wide blocks over 8 K ranges)."""
     K, N = 28672, 8192
     W = _w4(320, N, K)
     x = _spiked(321 + M, M, K, per_row=4)
@@ -152,8 +152,8 @@ def test_down_projection_70b_with_spiked_input(M):
 
 @pytest.mark.parametrize("M,K,N", [(64, 28672, 8192), (40, 16384, 512), (16, 16384, 1024)])
 def test_gemm_two_tiles_per_wave_long_k(M, K, N):
-    """Two column tiles per wave at K >= 16384: the 80-layer step's down
-    projection (64 rows, 16-row tiles x 4), 40 rows (x 3) and 16 rows (x 1),
+    """K >= 16384: the 80-layer step's down projection (64 rows, wide blocks),
+    few columns at 40 and at 16 rows (K-split workgroups of 8 and 16 waves),
     with residual; sampled columns where N is large."""
     W = _w4(330 + M, N, K)
     x = gen.normal_f16(331, M, (M, K))
@@ -183,12 +183,9 @@ def test_tp4_shard_gemms(name, K, N, res):
 
 @pytest.mark.parametrize("M", [8, 12])
 def test_tp4_shard_swiglu(M):
-    """K = 8192, N = 7168.  M = 8 (the shard's batch): one workgroup per
-    16-column tile, gate and up tile together, K split across 4 waves.
-    M = 12 (past the K-split SwiGLU's 8 rows): 112 column blocks of 64,
-    fewer than the compute units, so stream-K splits them between
-    workgroups and the fix-up kernel sums the gate and up partials in order
-    before silu(g) * u."""
+    """K = 8192, N = 7168 at 8 (the shard's batch) and 12 rows: one workgroup
+    per two 16-column tiles, gate and up tiles together, K split across 8
+    waves."""
     K, N = 8192, 7168
     Wg, Wu = _w4(350, N, K), _w4(351, N, K)
     x = gen.normal_f16(352, M, (M, K))
