@@ -162,7 +162,7 @@ def _stream(stream=None):
 # ------------------------------------------------------------------ helpers
 
 def workspace(nbytes: int, device="cuda"):
-    """A zero-filled device workspace (its header counters start at zero)."""
+    """A zero-filled device workspace (its header must start at zero)."""
     import torch
     return torch.zeros(int(nbytes), dtype=torch.uint8, device=device)
 

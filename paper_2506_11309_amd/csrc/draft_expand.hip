@@ -37,7 +37,6 @@ struct TopkArgs {
   int ldl, n, V, k, S, chunk;  // S workgroups per row, each `chunk` 16-byte vectors
   int32_t* tokens;
   float* logprobs;
-  void* ws;
   uint64_t* part;   // [n][kTopK][S] sort keys
   uint64_t* stats;  // [n][S] (s bits << 32 | m bits)
 };
@@ -281,11 +280,11 @@ size_t topk_logprobs_part_bytes(int n) {
 }
 
 void launch_topk_logprobs(const uint16_t* logits, int ldl, int n, int V, int k, int32_t* tokens, float* logprobs,
-                          void* ws, void* part, hipStream_t st) {
+                          void* part, hipStream_t st) {
   const int S = topk_logprobs_splits(n);
   const int nvec = V >> 3;
   uint64_t* p = reinterpret_cast<uint64_t*>(part);
-  TopkArgs a{logits, ldl, n, V, k, S, (nvec + S - 1) / S, tokens, logprobs, ws, p, p + (size_t)n * S * kTopK};
+  TopkArgs a{logits, ldl, n, V, k, S, (nvec + S - 1) / S, tokens, logprobs, p, p + (size_t)n * S * kTopK};
   // an index in a range fits 16 bits (the last range holds up to 7 columns more)
   if ((size_t)a.chunk * 8 + 8 <= 65536) hipLaunchKernelGGL(topk_ranges_kernel<uint32_t>, dim3(n * S), dim3(256), 0, st, a);
   else hipLaunchKernelGGL(topk_ranges_kernel<uint64_t>, dim3(n * S), dim3(256), 0, st, a);

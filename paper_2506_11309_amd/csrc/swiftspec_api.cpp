@@ -57,11 +57,14 @@ int check_w4(const swiftspec_w4* W) {
   return SWIFTSPEC_OK;
 }
 
-constexpr int kMaxCounters = (int)((SWIFTSPEC_WS_HEADER_BYTES - 256u) / 4u);
+// The attention entry points accept up to this many (KV head, 64 query rows)
+// blocks.  (The workspace header once held a counter for each; the bound
+// stays part of the interface.)
+constexpr long kMaxAttnBlocks = (SWIFTSPEC_WS_HEADER_BYTES - 256u) / 4u;
 
-bool attn_counters_fit(int T, int Hq, int Hkv) {
+bool attn_blocks_fit(int T, int Hq, int Hkv) {
   const long R = (long)T * (Hq / Hkv);
-  return (long)Hkv * ((R + 63) / 64) <= kMaxCounters;
+  return (long)Hkv * ((R + 63) / 64) <= kMaxAttnBlocks;
 }
 
 // what a GEMM of M rows needs
@@ -115,8 +118,8 @@ bool norm_in_gemm(const swiftspec_w4* W0, bool swiglu, const NormIn& n, int M, c
 }
 
 void run_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16_t* aprep, int M,
-              uint16_t* y, int ldy, uint16_t* yprep, const uint16_t* res, int ldr, void* ws,
-              float* part, hipStream_t st, const NormIn* norm = nullptr) {
+              uint16_t* y, int ldy, uint16_t* yprep, const uint16_t* res, int ldr, float* part,
+              hipStream_t st, const NormIn* norm = nullptr) {
   const bool swiglu = W1 != nullptr;
   ss::GemmPlan p = ss::plan_w4a16_gemm(M, W0->K, W0->N, swiglu);
   ss::GemmLaunch L;
@@ -153,12 +156,12 @@ void run_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16_t* ap
 // where its plan splits K within workgroups, else the norm kernel writes
 // the prepared operand into xprep and the GEMM reads it.
 void run_norm_gemm(const swiftspec_w4* W0, const swiftspec_w4* W1, const NormIn& n, int M, uint16_t* y,
-                   int ldy, uint16_t* yprep, uint16_t* xprep, void* ws, float* part, hipStream_t st) {
+                   int ldy, uint16_t* yprep, uint16_t* xprep, float* part, hipStream_t st) {
   if (norm_in_gemm(W0, W1 != nullptr, n, M, y, ldy)) {
-    run_gemm(W0, W1, nullptr, M, y, ldy, yprep, nullptr, 0, ws, part, st, &n);
+    run_gemm(W0, W1, nullptr, M, y, ldy, yprep, nullptr, 0, part, st, &n);
   } else {
     ss::launch_rmsnorm(n.x, M, W0->K, n.ldx, n.gamma, n.eps, nullptr, 0, xprep, st);
-    run_gemm(W0, W1, xprep, M, y, ldy, yprep, nullptr, 0, ws, part, st);
+    run_gemm(W0, W1, xprep, M, y, ldy, yprep, nullptr, 0, part, st);
   }
 }
 
@@ -170,7 +173,7 @@ void run_gemm_plain(const swiftspec_w4* W0, const swiftspec_w4* W1, const uint16
   uint16_t* aprep = reinterpret_cast<uint16_t*>(base + kHeader);
   float* part = reinterpret_cast<float*>(base + kHeader + align_up(p.prep_bytes));
   ss::launch_prepare_activations(x, M, ldx, W0->K, aprep, st);
-  run_gemm(W0, W1, aprep, M, y, ldy, nullptr, res, ldr, ws, part, st);
+  run_gemm(W0, W1, aprep, M, y, ldy, nullptr, res, ldr, part, st);
 }
 
 int check_tree_attention_args(const uint16_t* q, int ldq, const uint16_t* k, const uint16_t* v,
@@ -185,7 +188,7 @@ int check_tree_attention_args(const uint16_t* q, int ldq, const uint16_t* k, con
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(kc) || !aligned16(vc))
     return SWIFTSPEC_MISALIGNED;
   if (ldq % 8 || ldkv % 8) return SWIFTSPEC_MISALIGNED;
-  if (!attn_counters_fit(T, Hq, Hkv)) return SWIFTSPEC_UNSUPPORTED;
+  if (!attn_blocks_fit(T, Hq, Hkv)) return SWIFTSPEC_UNSUPPORTED;
   return SWIFTSPEC_OK;
 }
 
@@ -473,7 +476,7 @@ int swiftspec_rmsnorm_w4a16_gemm(const swiftspec_w4* W, const uint16_t* x, int32
   char* base = static_cast<char*>(ws);
   run_norm_gemm(W, nullptr, NormIn{x, ldx, gamma, eps}, M, y, ldy, nullptr,
                 reinterpret_cast<uint16_t*>(base + kHeader),
-                ws, reinterpret_cast<float*>(base + kHeader + align_up(p.prep_bytes)), S(stream));
+                reinterpret_cast<float*>(base + kHeader + align_up(p.prep_bytes)), S(stream));
   return check_launch();
 }
 
@@ -489,7 +492,7 @@ int swiftspec_rmsnorm_w4a16_swiglu(const swiftspec_w4* Wg, const swiftspec_w4* W
   char* base = static_cast<char*>(ws);
   run_norm_gemm(Wg, Wu, NormIn{x, ldx, gamma, eps}, M, y, ldy, nullptr,
                 reinterpret_cast<uint16_t*>(base + kHeader),
-                ws, reinterpret_cast<float*>(base + kHeader + align_up(p.prep_bytes)), S(stream));
+                reinterpret_cast<float*>(base + kHeader + align_up(p.prep_bytes)), S(stream));
   return check_launch();
 }
 
@@ -520,7 +523,7 @@ int swiftspec_w4a16_gemm_prepared(const swiftspec_w4* W, const uint16_t* xp, int
   if (M == 0) return SWIFTSPEC_OK;
   ss::GemmPlan p = ss::plan_w4a16_gemm(M, W->K, W->N, false);
   if (ws_bytes < kHeader + align_up(p.part_bytes)) return SWIFTSPEC_WORKSPACE_TOO_SMALL;
-  run_gemm(W, nullptr, xp, M, y, ldy, nullptr, residual, ldr, ws,
+  run_gemm(W, nullptr, xp, M, y, ldy, nullptr, residual, ldr,
            reinterpret_cast<float*>(static_cast<char*>(ws) + kHeader), S(stream));
   return check_launch();
 }
@@ -539,7 +542,7 @@ int swiftspec_w4a16_swiglu_prepared(const swiftspec_w4* Wg, const swiftspec_w4* 
   if (M == 0) return SWIFTSPEC_OK;
   ss::GemmPlan p = ss::plan_w4a16_gemm(M, Wg->K, Wg->N, true);
   if (ws_bytes < kHeader + align_up(p.part_bytes)) return SWIFTSPEC_WORKSPACE_TOO_SMALL;
-  run_gemm(Wg, Wu, xp, M, y, ldy, nullptr, nullptr, 0, ws,
+  run_gemm(Wg, Wu, xp, M, y, ldy, nullptr, nullptr, 0,
            reinterpret_cast<float*>(static_cast<char*>(ws) + kHeader), S(stream));
   return check_launch();
 }
@@ -725,7 +728,7 @@ int swiftspec_topk_logprobs(const uint16_t* logits, int32_t ldl, int32_t n, int3
   if (n > SWIFTSPEC_MAX_TREE || k > 8) return SWIFTSPEC_UNSUPPORTED;
   if (!aligned16(logits) || ldl % 8) return SWIFTSPEC_MISALIGNED;
   if (ws_bytes < swiftspec_topk_logprobs_workspace_bytes(n)) return SWIFTSPEC_WORKSPACE_TOO_SMALL;
-  ss::launch_topk_logprobs(logits, ldl, n, V, k, d_tokens, d_logprobs, ws, static_cast<char*>(ws) + kHeader,
+  ss::launch_topk_logprobs(logits, ldl, n, V, k, d_tokens, d_logprobs, static_cast<char*>(ws) + kHeader,
                            S(stream));
   return check_launch();
 }
@@ -751,7 +754,7 @@ static int check_layer(const swiftspec_layer* Lw, const swiftspec_dims* d, int32
   if (T < 1 || d->H < 1 || d->Hq < 1 || d->Hkv < 1 || d->F < 1 || d->S_max < T) return SWIFTSPEC_INVALID_ARG;
   if (T > SWIFTSPEC_MAX_TREE || (d->D != 64 && d->D != 128) || d->Hq % d->Hkv) return SWIFTSPEC_UNSUPPORTED;
   const int H = d->H, Hd = d->Hq * d->D, Nqkv = (d->Hq + 2 * d->Hkv) * d->D, F = d->F;
-  if (!attn_counters_fit(T, d->Hq, d->Hkv)) return SWIFTSPEC_UNSUPPORTED;
+  if (!attn_blocks_fit(T, d->Hq, d->Hkv)) return SWIFTSPEC_UNSUPPORTED;
   int rc;
   if ((rc = check_w4(&Lw->wqkv)) || (rc = check_w4(&Lw->wo)) || (rc = check_w4(&Lw->wgate)) ||
       (rc = check_w4(&Lw->wup)) || (rc = check_w4(&Lw->wdown)))
@@ -780,13 +783,13 @@ static void enqueue_layer(const swiftspec_layer* Lw, const swiftspec_dims* d, ui
   // the RMSNorms in front of the QKV and the FFN projections run with them
   // (swiftspec_rmsnorm_w4a16_gemm / _swiglu)
   const NormIn n_attn{hidden, H, Lw->attn_norm, d->eps}, n_mlp{h, H, Lw->mlp_norm, d->eps};
-  run_norm_gemm(&Lw->wqkv, nullptr, n_attn, T, qkv, Nqkv, nullptr, xn_p, ws, part, st);
+  run_norm_gemm(&Lw->wqkv, nullptr, n_attn, T, qkv, Nqkv, nullptr, xn_p, part, st);
   run_attention(qkv, Nqkv, qkv + Hd, qkv + Hd + d->Hkv * d->D, Nqkv, Lw->k_cache, Lw->v_cache,
                 d->S_max, d_prefix_len, d_parent, T, d->Hq, d->Hkv, d->D, rope,
                 1.0f / std::sqrt((float)d->D), o, Hd, o_p, ws, part, st);
-  run_gemm(&Lw->wo, nullptr, o_p, T, h, H, nullptr, hidden, H, ws, part, st);
-  run_norm_gemm(&Lw->wgate, &Lw->wup, n_mlp, T, m, F, m_p, hn_p, ws, part, st);
-  run_gemm(&Lw->wdown, nullptr, m_p, T, hidden, H, nullptr, h, H, ws, part, st);
+  run_gemm(&Lw->wo, nullptr, o_p, T, h, H, nullptr, hidden, H, part, st);
+  run_norm_gemm(&Lw->wgate, &Lw->wup, n_mlp, T, m, F, m_p, hn_p, part, st);
+  run_gemm(&Lw->wdown, nullptr, m_p, T, hidden, H, nullptr, h, H, part, st);
 }
 
 int swiftspec_verify_layer(const swiftspec_layer* Lw, const swiftspec_dims* d, uint16_t* hidden,
