@@ -522,10 +522,14 @@ __global__ __launch_bounds__(256) void w4a16_fixup_kernel(GemmArgs a) {
 // 128) over one of S equal K ranges, two tiles per wave, and a step is one
 // 128-k group.  The activation fragments of a group are read from L2 once
 // per 16 weight tiles (4 or 8 in the stream-K kernel) and shared through a
-// 3-slot LDS ring.  What bounds it is instruction issue: per group a SIMD's
-// two waves have 8 MT MFMAs each and the dequantisation of two blocks, and
-// with one workgroup per compute unit nothing hides a wave that does one
-// after the other.  So a step interleaves them: the products of each M-tile
+// 3-slot LDS ring.  What bounds it is each SIMD's own work: per group its two
+// waves have 8 MT MFMAs each and the dequantisation of two blocks, and with
+// one workgroup per compute unit nothing hides a wave that does one after the
+// other.  (K 8192, N 28672 SwiGLU by counters, 64 / 32 rows: matrix cores busy
+// 45 / 28 % of the cycles, the vector ALUs 55 / 53 %, one or the other 83 / 70
+// %; LDS reads 51 / 32 % of its bandwidth, waits for it 5 / 2 % of the waves'
+// cycles; the weight stream 53 / 70 % of the read rate.)  So a step
+// interleaves them: the products of each M-tile
 // stand beside the LDS reads of the next M-tile's fragments, the previous
 // M-tile's group sums times their scales, and a share of the next group's
 // dequantisation; no instruction waits for the MFMA just issued.  Loads are
@@ -535,8 +539,9 @@ __global__ __launch_bounds__(256) void w4a16_fixup_kernel(GemmArgs a) {
 // adds them in range order (deterministic).
 // Measured against the stream-K kernel (us, weights rotated through HBM; 32
 // / 45 / 64 rows): SwiGLU K 8192, N 28672 59.0 -> 58.3, 74.6 -> 69.1, 94.2
-// -> 83.8 (3.0 TB/s of weights at 64 rows); K 28672, N 8192 at 45 and 64
-// rows 44.4 -> 42.0, 53.6 -> 48.0.
+// -> 83.8 (3.0 TB/s of weights at 64 rows); K 28672, N 8192 39.0 -> 36.2,
+// 44.4 -> 42.0, 53.6 -> 48.0.  (At 32 rows the SwiGLU is within 1 % of it by
+// itself and 2 us faster in the 70B layer.)
 constexpr int kWideW = 8;     // waves of a workgroup
 constexpr int kWideStep = 4;  // K ranges are multiples of this many groups (the register ring's length)
 
@@ -828,12 +833,12 @@ __global__ __launch_bounds__(256) void w4a16_wide_fixup_kernel(GemmArgs a) {
 // stay on the stream-K kernel, which shares the activations through LDS.
 // Up to 16 rows the rest is fixed cost (launch, first loads, the sum).
 // Measured against the kernels used before (us, weights rotated through
-// HBM; 8 / 32 / 64 rows): K 4096, N 4096 5.6 -> 4.9, 10.0 -> 5.8, 11.8 ->
-// 8.6; K 8192, N 8192 14.3 -> 12.2, 20.8 -> 15.1, 23.9 -> 21.0; K 8192, N
-// 10240 17.7 -> 14.6, 23.3 -> 19.5, 27.8 -> 26.6; K 2048, N 8192 6.0 ->
-// 4.5, 9.4 -> 5.3, 11.8 -> 6.7; SwiGLU K 8192, N 7168 16.5 -> 15.1, 28.3
-// -> 19.3, 32.9 -> 26.0; SwiGLU K 4096, N 14336 17.9 -> 15.9, 23.3 -> 19.2,
-// 32.5 -> 29.5.
+// HBM, the plain ones with a residual; 8 / 32 / 64 rows): K 4096, N 4096 6.5
+// -> 5.4, 10.2 -> 7.2, 12.6 -> 10.2; K 8192, N 8192 16.0 -> 13.3, 22.6 ->
+// 15.5, 25.9 -> 22.0; K 8192, N 10240 18.5 -> 16.7, 23.9 -> 19.8, 28.4 ->
+// 27.8; K 2048, N 8192 7.0 -> 5.1, 10.1 -> 5.9, 12.3 -> 7.8; SwiGLU K 8192, N
+// 7168 17.1 -> 16.6, 30.6 -> 21.3, 34.6 -> 27.8; SwiGLU K 4096, N 14336 18.4
+// -> 17.2, 24.5 -> 22.0, 34.1 -> 31.2.
 
 // The W waves' partial sums of a K-split workgroup (red, after the barrier)
 // added in wave order, and the workgroup's MT x kC output tiles written,
@@ -1357,15 +1362,17 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
     if (MT == 2 && tiles > 1024) return;
     if (MT == 4 && tiles > 512 && tiles < 832 && K > 3584) return;
     // above 32 rows at more than one workgroup per compute unit only for a
-    // short K (K 5888, N 10816, 64 rows: 34.5 against 36.4 us)
+    // short K (K 5888, N 10816, 64 rows: 34.5 against 36.4 us, weights from the
+    // Infinity Cache; from HBM K 6144 .. 20480, N 9216 1.1 .. 1.4 of stream-K)
     if (tiles > 512 && MT >= 3 && (K > 4096 || tiles > 1024)) return;
     // gate + up of one column tile up to one workgroup per compute unit, and
-    // where the activations are short or few (N 8640, K 3072, 4 rows: 10.2
-    // against 11.7 us; 29 rows 14.6 against 14.9; N 7808, K 4608, 1 and 8 rows:
-    // 12.2 and 12.7 against 12.8 and 13.2)
+    // where the activations are short or few (weights from the Infinity Cache:
+    // N 8640, K 3072, 4 rows: 10.2 against 11.7 us; 29 rows 14.6 against 14.9;
+    // N 7808, K 4608, 1 and 8 rows: 12.2 and 12.7 against 12.8 and 13.2)
     p.knt = tiles <= 256 || (MT == 1 && K <= 2560) || (M <= 8 && (tiles > 512 || K <= 5120)) ? 2 : 4;
     // with about two workgroups per compute unit four waves each (K 4096, N
-    // 14336, 16 rows: 15.7 against 17.7 us with eight)
+    // 14336, 16 rows: 15.7 against 17.7 us with eight, weights from the
+    // Infinity Cache)
     p.ksw = p.knt == 4 && tiles > 512 && MT <= 3 ? 4 : 8;
     return;
   }
@@ -1419,18 +1426,21 @@ static void plan_ksplit(int MT, int M, int K, int tiles, bool swiglu, GemmPlan& 
     p.knt = K <= 2048 && MT <= 2 ? 2 : 4;
   }
   // 16 waves where one M-tile leaves the registers and K the groups (K 14336,
-  // N 4096, 8 rows: 10.9 against 14.0 us with 8)
+  // N 4096, 8 rows: 10.9 against 14.0 us with 8, weights from the Infinity Cache)
   p.ksw = MT == 1 && G >= 32 && p.knt <= 2 ? 16 : 8;
 }
 
 // Wide blocks (p.wide): where the matrix is large enough that a workgroup per
 // compute unit and K range has a long run of groups.  Lines from sweeps over 18
 // SwiGLU and 26 plain shapes (K 1536 .. 28672, N 2112 .. 32384) at 29, 45 and
-// 64 rows against the other two forms; S is the number of K ranges that
-// fills one round of the 256 compute units (two rounds were slower at every
-// shape: K 8192, N 26752, 64 rows 76 us at S = 1, 85 at 2), and shapes whose
-// round would stay under 200 workgroups (144 with S = 1, which needs no
-// partials) keep the other forms.
+// 64 rows against the other two forms, weights from the Infinity Cache unless
+// said otherwise; above 32 rows 350 shapes that they choose wide blocks for
+// took 0.69 to 1.06 of stream-K's time with weights from HBM, one more than
+// 1.03 (K 16384, N 6144).  S is the number of K ranges that fills one round of
+// the 256 compute units (two rounds were slower at every shape: K 8192, N
+// 26752, 64 rows 76 us at S = 1, 85 at 2), and shapes whose round would stay
+// under 200 workgroups (144 with S = 1, which needs no partials) keep the
+// other forms.
 static void plan_wide(int MT, int K, int tiles, bool swiglu, GemmPlan& p) {
   if (MT < 2 || tiles < 1 || K % (128 * kWideStep)) return;
   const int nb = (tiles + (swiglu ? 8 : 16) - 1) / (swiglu ? 8 : 16);
