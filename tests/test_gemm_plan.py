@@ -216,7 +216,7 @@ def test_every_instance_the_plan_reaches_runs_in_a_gpu_test(plan, norm, gpu_test
     reached, tested = set(), set()
     for swiglu in (False, True):
         for K in KS + (1024, 1152, 1408, 1920, 2048, 2176, 16512, 20864):
-            for N in NS + (1024, 4160, 6144, 8256, 16384, 17472):
+            for N in NS + (1024, 4160, 6144, 8256, 16384, 17472, 32768):
                 for M in ROWS:
                     p = plan(M, K, N, swiglu)
                     reached.add(_instance(p, M, K, N, swiglu))

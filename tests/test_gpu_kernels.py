@@ -422,6 +422,8 @@ def test_w4a16_wide_blocks(M, K, N, swiglu):
     (8, 8320, 17472, False), (8, 8320, 17408, False), (17, 12800, 2048, False), (17, 16512, 2048, False),
     (40, 8320, 2048, False), (40, 16512, 2048, False), (64, 8320, 2048, False), (64, 16512, 2048, False),
     (64, 6272, 2048, False),
+    # plain, whole blocks of one K step, 2 to 4 M-tiles
+    (17, 128, 32768, False), (40, 128, 32768, False), (64, 128, 32768, False),
     # SwiGLU: whole blocks, a K that is no multiple of the wide blocks' step; split blocks
     (16, 1152, 17472, True), (32, 1152, 17472, True), (47, 1152, 17472, True), (64, 1152, 17472, True),
     (9, 20864, 832, True), (17, 20864, 832, True), (40, 4224, 10240, True), (64, 4096, 8256, True)])
